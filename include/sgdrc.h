@@ -318,10 +318,12 @@ int colour_alloc_pagetable(sgdrc_ctx *ctx, const sgdrc_hash *hash, uint64_t addr
  * ``stream``, the count of qualifying pages in the pool goes to *d_n_found
  * (device memory, one uint64, 8-byte aligned) instead of a host variable,
  * and a shortfall is no error: the caller compares *d_n_found with
- * n_needed (d_pt then holds all the qualifying pages).  Its scratch is a
- * fixed 192.25 KiB block of the library's own device memory, one per
- * device and held until the process ends, which limits pool_pages to 2^26.
- * Every call on a device shares that block: calls that overlap on one GPU
+ * n_needed (d_pt then holds all the qualifying pages).  Pools have at most
+ * 2^26 pages.  Hashes whose masks have full rank on the lowest page-number
+ * bits (so that every aligned run of at most 4096 pages holds the colours
+ * equally often) need no scratch.  Other hashes use a fixed 8 KiB block of
+ * the library's own device memory, one per device and held until the process
+ * ends, which every call on a device shares: calls that overlap on one GPU
  * (on different streams or host threads) race, and the caller must order
  * them.  Every scratch word a call reads is first written by the same
  * call, so nothing needs clearing between calls.  EINVAL: as

@@ -13,10 +13,9 @@
 // last n mod 16 addresses are coloured by the grid's last workgroup.
 //
 // The page-table build is an ordered stream compaction over the pool's page
-// addresses: a counting pass, a scan of per-workgroup counts, and an
-// emitting pass that places each qualifying page with a wavefront ballot
-// and a masked bit count, so the table comes out in ascending page order
-// regardless of scheduling.
+// addresses.  For most XOR hashes the rank of a run of pages is a product,
+// and one launch places every page; other hashes and colour tables take a
+// counting and an emitting pass.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -264,118 +263,327 @@ __global__ __launch_bounds__(kClsThreads) void k_classify_finish(const uint64_t 
     }
 }
 
+// ------------------------------------------------- page-table build
+//
+// Both builds below place each qualifying page by its rank: the number of
+// qualifying pages before its workgroup's pages, plus its rank inside the
+// workgroup from wavefront ballots and masked bit counts, so the table comes
+// out in ascending page order whatever the scheduling.
 constexpr int kPtThreads = 256;
-constexpr int kPtIters = 16;
-constexpr uint64_t kPtBlockPages = (uint64_t)kPtThreads * kPtIters;
+constexpr uint32_t kPtWaves = kPtThreads / 64;
 
-// One pass of the ordered compaction.  Workgroup b covers pages
-// [b*4096, (b+1)*4096) in 16 rounds of 256 consecutive pages.  The counting
-// pass writes the number of qualifying pages per workgroup; the emitting
-// pass writes each qualifying page at its rank among all qualifying pages.
-// Page tests.  QXor: the colour of the page's base address is in the
-// set given to the kernel, which the host has narrowed to the colours whose
-// whole page lies in the caller's set (see page_colour_set).  QTable: every
-// partition that the page touches is in the table and has a colour in the
-// set.
+// The rank of this thread's first qualifying page among the workgroup's
+// pages, for threads whose ``V`` consecutive pages qualify by the bits of
+// ``m``; ``sum`` becomes the workgroup's count.  One barrier; s_wave is free
+// again after the caller's next one.
+template <int V>
+__device__ __forceinline__ uint32_t pt_rank(uint32_t m, uint32_t *s_wave, uint32_t &sum)
+{
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    uint32_t below = 0u, mine = 0u;
+    if (V <= 4) {
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const uint64_t bal = __ballot((m >> k) & 1u);
+            below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)bal, below));
+            mine += (uint32_t)__popcll(bal);
+        }
+    } else {
+        // the counts (at most 16) by their bits
+        const uint32_t c = (uint32_t)__popc(m);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const uint64_t bal = __ballot((c >> k) & 1u);
+            below += __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u)) << k;
+            mine += (uint32_t)__popcll(bal) << k;
+        }
+    }
+    if (lane == 0)
+        s_wave[wave] = mine;
+    __syncthreads();
+    uint32_t before = 0u;
+    sum = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < kPtWaves; ++w) {
+        const uint32_t cw = s_wave[w];
+        before += w < wave ? cw : 0u;
+        sum += cw;
+    }
+    return before + below;
+}
+
+// XOR hashes, one launch.  The colour of page number q (address >> shift) is
+// linear over GF(2) in q, so when every aligned run of 2^m pages holds the
+// same number ``per_run`` of qualifying pages (the host checks it, see
+// plan_runs), the rank of a run's first page is a product and no counting
+// pass is needed.  Workgroup w takes run w of 2^m = 1024 R pages counted
+// from the run that holds the pool's first page ``q0``; ``skip`` is the
+// number of qualifying pages of that first run before q0, and ``total`` the
+// qualifying pages of the pool (both from the host).  Each thread takes four
+// consecutive pages of an aligned group, whose colours differ from the first
+// one's by the constants v0 and v1.
+//
+// Bound by the launch and one chain of dependent steps (no data is read).
+// 409600 pages, 8 of 64 colours, 49152 entries, on MI355X: 3.2 us, and 20.0
+// us for the synchronous call, against 6.1 + 4.6 + 7.6 us for a counting, a
+// scanning and an emitting launch, and 35.3 us with them and a copy of the
+// count.  2^26 pages, 2^22 entries: call 44 against 247 us.
+template <int K>
+__global__ __launch_bounds__(kPtThreads) void k_pt_runs(HashArgs h, uint64_t q0, uint32_t shift,
+                                                        uint64_t pool_pages, SetArgs set, uint32_t R,
+                                                        uint32_t per_run, uint32_t skip,
+                                                        uint32_t v0, uint32_t v1, uint32_t *pt,
+                                                        uint64_t n_needed, uint64_t total,
+                                                        uint64_t *d_total)
+{
+    __shared__ uint32_t s_set[8];
+    __shared__ uint32_t s_wave[kPtWaves];
+    if (d_total && blockIdx.x == 0 && threadIdx.x == 0)
+        *d_total = total;
+    if (n_needed == 0)
+        return;
+    if (threadIdx.x < 8)
+        s_set[threadIdx.x] = set.w[threadIdx.x];
+    __syncthreads();
+    const uint64_t run = 1024ull * R;
+    const uint64_t first = (q0 / run + blockIdx.x) * run;
+    uint64_t running = (uint64_t)blockIdx.x * per_run;
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint64_t q = first + r * 1024u + threadIdx.x * 4u;
+        const uint64_t a = q << shift;
+        const uint32_t c = colour_of<K>((uint32_t)a, (uint32_t)(a >> 32), h);
+        uint32_t m = 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            const uint32_t ck = c ^ (k & 1u ? v0 : 0u) ^ (k & 2u ? v1 : 0u);
+            m |= ((s_set[ck >> 5] >> (ck & 31u)) & 1u) << k;
+        }
+        uint32_t sum;
+        uint64_t rank = running + pt_rank<4>(m, s_wave, sum);
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            if ((m >> k) & 1u) {
+                // pages before q0 (only in the first run) and past the pool
+                // are counted in the ranks and not written
+                const uint64_t page = q + k - q0;
+                if (page < pool_pages && rank - skip < n_needed)
+                    pt[rank - skip] = (uint32_t)page;
+                ++rank;
+            }
+        }
+        running += sum;
+        __syncthreads();
+    }
+}
+
+// Any other page test, two launches: the counting pass writes the number of
+// qualifying pages of each workgroup's chunk, the emitting pass sums the
+// counts before its own and places its pages.  At most kPtMaxChunks
+// workgroups, so that the sum is a few loads per thread and needs no scan
+// launch between the two.  Each thread tests up to Q::kPages consecutive pages
+// at a time; the emitting pass collects a round's entries in LDS and stores them in
+// order, and ends once the table is full.
+//
+// 2^24 1 KiB pages tested through a colour table of as many partitions, a
+// quarter of them qualifying, 2^20 entries, on MI355X: 5.8 + 6.7 us, against
+// 29.6 + 9.0 + 30.0 us with one byte load per page and 16 barriers per
+// workgroup and a scan in between.  2^25 pages of two partitions: call 62
+// against 200 us; 2^20 pages of 64 partitions 46 against 381 us.  2048
+// chunks keep every wavefront slot of the chip filled (1024: 2^26 pages 68
+// against 55 us).
+constexpr uint32_t kPtMaxChunks = 2048;
+
+// QXor: the colour of the page's base address is in the set given to the
+// kernel, which the host has narrowed to the colours whose whole page lies in
+// the caller's set (see page_colour_set).
 template <int K>
 struct QXor {
+    static constexpr int kPages = 4;
     HashArgs h;
-    __device__ bool operator()(uint64_t a, const uint32_t *s_set) const
+    __device__ uint32_t pages() const { return kPages; }
+    __device__ uint32_t operator()(uint64_t a, uint32_t page_shift, uint64_t, const uint32_t *s_set) const
     {
-        const uint32_t c = colour_of<K>((uint32_t)a, (uint32_t)(a >> 32), h);
-        return ((s_set[c >> 5] >> (c & 31u)) & 1u) != 0u;
+        uint32_t m = 0u;
+#pragma unroll
+        for (int k = 0; k < kPages; ++k) {
+            const uint64_t ak = a + ((uint64_t)k << page_shift);
+            const uint32_t c = colour_of<K>((uint32_t)ak, (uint32_t)(ak >> 32), h);
+            m |= ((s_set[c >> 5] >> (c & 31u)) & 1u) << k;
+        }
+        return m;
     }
 };
 
+// QTable: every partition that the page touches is in the table and has a
+// colour in the set.  ALIGNED: a page is 2^log_parts <= 16 whole partitions,
+// so that a thread reads the colours of 16 partitions with one load (any
+// alignment) where all of them lie in the table; otherwise a thread tests one
+// page at a time.
+template <bool ALIGNED>
 struct QTable {
+    static constexpr int kPages = ALIGNED ? 16 : 1;
     TableArgs t;
-    uint32_t page_shift;
-    __device__ bool operator()(uint64_t a, const uint32_t *s_set) const
+    uint32_t log_parts;
+    __device__ uint32_t pages() const { return ALIGNED ? 16u >> log_parts : 1u; }
+    // bits of the 16 partitions from j on whose colours are in the set
+    // (255 is never in it)
+    __device__ __forceinline__ uint32_t has16(uint64_t j, const uint32_t *s_set) const
+    {
+        u32x4 v;
+        __builtin_memcpy(&v, t.lut + j, sizeof v);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        uint32_t m = 0u;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t c = (w[k >> 2] >> (8 * (k & 3))) & 0xffu;
+            m |= ((s_set[c >> 5] >> (c & 31u)) & 1u) << k;
+        }
+        return m;
+    }
+    __device__ bool one(uint64_t a, uint32_t page_shift, const uint32_t *s_set) const
     {
         if (a < t.origin)
             return false;
-        const uint64_t j0 = (a - t.origin) >> t.shift;
+        uint64_t j = (a - t.origin) >> t.shift;
         const uint64_t j1 = (a + (1ull << page_shift) - 1u - t.origin) >> t.shift;
         if (j1 >= t.entries)
             return false;
         bool ok = true;
-        for (uint64_t j = j0; j <= j1 && ok; ++j) {
+        for (; ok && j1 - j >= 15u && j <= j1; j += 16u)
+            ok = has16(j, s_set) == 0xffffu;
+        for (; ok && j <= j1; ++j) {
             const uint32_t c = t.lut[j];
-            ok = c != 255u && ((s_set[c >> 5] >> (c & 31u)) & 1u) != 0u;
+            ok = ((s_set[c >> 5] >> (c & 31u)) & 1u) != 0u;
         }
         return ok;
     }
+    // the first ``n`` (at most pages()) of the pages from address a on
+    __device__ uint32_t operator()(uint64_t a, uint32_t page_shift, uint64_t n, const uint32_t *s_set) const
+    {
+        const uint64_t j = (a - t.origin) >> t.shift;
+        if (ALIGNED && a >= t.origin && t.entries >= 16u && j <= t.entries - 16u) {
+            uint32_t m = has16(j, s_set);
+            if (log_parts == 0u)
+                return m;
+            for (uint32_t d = 1u; d < 1u << log_parts; d <<= 1)
+                m &= m >> d;
+            uint32_t out = 0u;
+            for (uint32_t k = 0; k < 16u >> log_parts; ++k)
+                out |= ((m >> (k << log_parts)) & 1u) << k;
+            return out;
+        }
+        uint32_t m = 0u;
+        for (uint32_t k = 0; k < pages() && k < n; ++k)
+            m |= (one(a + ((uint64_t)k << page_shift), page_shift, s_set) ? 1u : 0u) << k;
+        return m;
+    }
 };
 
-template <class Q, bool EMIT>
-__global__ __launch_bounds__(kPtThreads) void k_pt_pass(Q qual, uint64_t origin, uint32_t shift,
-                                                        uint64_t pool_pages, SetArgs set,
-                                                        uint32_t *block_counts,
-                                                        const uint64_t *block_offsets,
-                                                        uint32_t *pt, uint64_t n_needed)
+// Bits of the qualifying ones of this thread's pages [page, page + qual.pages()).
+template <class Q>
+__device__ __forceinline__ uint32_t pt_test(const Q &qual, uint64_t origin, uint32_t shift,
+                                            uint64_t page, uint64_t end, const uint32_t *s_set)
+{
+    if (page >= end)
+        return 0u;
+    const uint64_t n = end - page;
+    const uint32_t m = qual(origin + (page << shift), shift, n, s_set);
+    return n < (uint64_t)qual.pages() ? m & ((1u << n) - 1u) : m;
+}
+
+template <class Q>
+__global__ __launch_bounds__(kPtThreads) void k_pt_count(Q qual, uint64_t origin, uint32_t shift,
+                                                         uint64_t pool_pages, uint64_t chunk,
+                                                         SetArgs set, uint32_t *counts)
 {
     __shared__ uint32_t s_set[8];
-    __shared__ uint32_t s_wave[kPtThreads / 64];
+    __shared__ uint32_t s_count[kPtWaves];
     if (threadIdx.x < 8)
         s_set[threadIdx.x] = set.w[threadIdx.x];
     __syncthreads();
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-    const uint64_t base = (uint64_t)blockIdx.x * kPtBlockPages;
-    uint64_t running = EMIT ? block_offsets[blockIdx.x] : 0;
-    uint32_t total = 0;
-    for (int it = 0; it < kPtIters; ++it) {
-        const uint64_t page = base + (uint64_t)it * kPtThreads + threadIdx.x;
-        const bool q = page < pool_pages && qual(origin + (page << shift), s_set);
-        const uint64_t bal = __ballot(q);
-        const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-            (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-        if (lane == 0)
-            s_wave[wave] = (uint32_t)__popcll(bal);
-        __syncthreads();
-        uint32_t before = 0, sum = 0;
+    const uint64_t lo = (uint64_t)blockIdx.x * chunk;
+    const uint64_t end = pool_pages - lo < chunk ? pool_pages : lo + chunk;
+    uint32_t c = 0u;
+    const uint32_t each = qual.pages();
+    for (uint64_t p = lo + threadIdx.x * each; p < end; p += kPtThreads * each)
+        c += (uint32_t)__popc(pt_test(qual, origin, shift, p, end, s_set));
 #pragma unroll
-        for (uint32_t w = 0; w < kPtThreads / 64; ++w) {
-            const uint32_t cw = s_wave[w];
-            before += w < wave ? cw : 0u;
-            sum += cw;
-        }
-        if (EMIT && q) {
-            const uint64_t pos = running + before + below;
-            if (pos < n_needed)
-                pt[pos] = (uint32_t)page;
-        }
-        running += sum;
-        total += sum;
-        __syncthreads();
+    for (int off = 32; off >= 1; off >>= 1)
+        c += __shfl_xor(c, off, 64);
+    if ((threadIdx.x & 63u) == 0u)
+        s_count[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t v = 0u;
+#pragma unroll
+        for (uint32_t w = 0; w < kPtWaves; ++w)
+            v += s_count[w];
+        counts[blockIdx.x] = v;
     }
-    if (!EMIT && threadIdx.x == 0)
-        block_counts[blockIdx.x] = total;
 }
 
-// Exclusive scan of the per-workgroup counts (one workgroup, chunks of 1024).
-__global__ __launch_bounds__(1024) void k_pt_scan(const uint32_t *counts, uint64_t *offsets,
-                                                  uint64_t nblocks, uint64_t *total)
+// ``total`` (device or pinned host memory) receives the pool's count.
+template <class Q>
+__global__ __launch_bounds__(kPtThreads) void k_pt_emit(Q qual, uint64_t origin, uint32_t shift,
+                                                        uint64_t pool_pages, uint64_t chunk,
+                                                        SetArgs set, const uint32_t *counts,
+                                                        uint32_t n_chunks, uint32_t *pt,
+                                                        uint64_t n_needed, uint64_t *total)
 {
-    __shared__ uint64_t s[1024];
-    uint64_t carry = 0;
-    for (uint64_t base = 0; base < nblocks; base += 1024) {
-        const uint64_t i = base + threadIdx.x;
-        const uint64_t v = i < nblocks ? counts[i] : 0;
-        s[threadIdx.x] = v;
+    __shared__ uint32_t s_set[8];
+    __shared__ uint32_t s_wave[kPtWaves];
+    __shared__ uint64_t s_sum[2][kPtWaves];
+    __shared__ uint32_t s_out[kPtThreads * Q::kPages];
+    if (threadIdx.x < 8)
+        s_set[threadIdx.x] = set.w[threadIdx.x];
+    uint64_t before = 0u, all = 0u;
+#pragma unroll
+    for (uint32_t r = 0; r < kPtMaxChunks / kPtThreads; ++r) {
+        const uint32_t i = r * kPtThreads + threadIdx.x;
+        const uint32_t v = i < n_chunks ? counts[i] : 0u;
+        before += i < blockIdx.x ? v : 0u;
+        all += v;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        before += __shfl_xor(before, off, 64);
+        all += __shfl_xor(all, off, 64);
+    }
+    if ((threadIdx.x & 63u) == 0u) {
+        s_sum[0][threadIdx.x >> 6] = before;
+        s_sum[1][threadIdx.x >> 6] = all;
+    }
+    __syncthreads();
+    uint64_t running = 0u;
+    all = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < kPtWaves; ++w) {
+        running += s_sum[0][w];
+        all += s_sum[1][w];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *total = all;
+    const uint64_t lo = (uint64_t)blockIdx.x * chunk;
+    const uint64_t end = pool_pages - lo < chunk ? pool_pages : lo + chunk;
+    const uint32_t each = qual.pages();
+    for (uint64_t base = lo; base < end && running < n_needed; base += kPtThreads * each) {
+        const uint64_t p = base + threadIdx.x * each;
+        const uint32_t m = pt_test(qual, origin, shift, p, end, s_set);
+        uint32_t sum;
+        uint32_t rank = pt_rank<Q::kPages>(m, s_wave, sum);
+#pragma unroll
+        for (int k = 0; k < Q::kPages; ++k)
+            if ((m >> k) & 1u)
+                s_out[rank++] = (uint32_t)(p + k);
         __syncthreads();
-        for (uint32_t off = 1; off < 1024; off <<= 1) {
-            uint64_t t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-            __syncthreads();
-            s[threadIdx.x] += t;
-            __syncthreads();
-        }
-        if (i < nblocks)
-            offsets[i] = carry + s[threadIdx.x] - v;
-        carry += s[1023];
+        for (uint32_t i = threadIdx.x; i < sum; i += kPtThreads)
+            if (running + i < n_needed)
+                pt[running + i] = s_out[i];
+        running += sum;
         __syncthreads();
     }
-    if (threadIdx.x == 0)
-        *total = carry;
 }
 
 static HashArgs hash_args(const sgdrc_hash *h)
@@ -439,38 +647,6 @@ static int launch_classify_xor(Ctx *c, const HashArgs &h, const uint64_t *d_addr
     return launch_classify<K, false>(c, h, TableArgs{}, d_addrs, n, d_colours, d_hist, stream);
 }
 
-template <class Q>
-static int launch_pagetable(Ctx *c, const Q &q, uint64_t origin, uint32_t shift,
-                            uint64_t pool_pages, const SetArgs &set, uint64_t n_needed,
-                            uint32_t *d_pt, uint64_t nblocks, uint32_t *d_counts,
-                            uint64_t *d_offsets, uint64_t *d_total, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_pt_pass<Q, false>), dim3((uint32_t)nblocks), dim3(kPtThreads), 0, s, q,
-                       origin, shift, pool_pages, set, d_counts, (const uint64_t *)nullptr,
-                       (uint32_t *)nullptr, (uint64_t)0);
-    SGDRC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_pt_scan, dim3(1), dim3(1024), 0, s, (const uint32_t *)d_counts, d_offsets,
-                       nblocks, d_total);
-    SGDRC_HIP(hipGetLastError());
-    if (n_needed > 0) {
-        hipLaunchKernelGGL((k_pt_pass<Q, true>), dim3((uint32_t)nblocks), dim3(kPtThreads), 0, s,
-                           q, origin, shift, pool_pages, set, d_counts,
-                           (const uint64_t *)d_offsets, d_pt, n_needed);
-        SGDRC_HIP(hipGetLastError());
-    }
-    return SGDRC_OK;
-}
-
-template <int K>
-static int launch_pagetable_xor(Ctx *c, const HashArgs &h, uint64_t origin, uint32_t shift,
-                                uint64_t pool_pages, const SetArgs &set, uint64_t n_needed,
-                                uint32_t *d_pt, uint64_t nblocks, uint32_t *d_counts,
-                                uint64_t *d_offsets, uint64_t *d_total, hipStream_t s)
-{
-    return launch_pagetable(c, QXor<K>{h}, origin, shift, pool_pages, set, n_needed, d_pt, nblocks,
-                            d_counts, d_offsets, d_total, s);
-}
-
 // The set of base-address colours whose pages lie wholly in ``set``.  A
 // page holds every address base + o, o < 2^page_shift, and the hash is
 // linear over GF(2), so its bytes have exactly the colours c ^ l, with c the
@@ -509,7 +685,7 @@ static sgdrc_colour_set page_colour_set(const sgdrc_hash *h, uint32_t page_shift
     return out;
 }
 
-static std::mutex g_pt_mu;  // page-table scratch is per context; builds are serialised
+static std::mutex g_pt_mu;  // general builds share a context's scratch: serialised
 
 static int check_pool_args(uint64_t addr_origin, uint32_t page_shift, uint64_t pool_pages,
                            const sgdrc_colour_set *set, uint64_t n_needed, uint32_t *d_pt,
@@ -565,23 +741,16 @@ static int check_table(const sgdrc_colour_table *t)
     return SGDRC_OK;
 }
 
-// Scratch of one build: the scan's total (256 bytes, aligned), then the
-// per-workgroup offsets (uint64) and counts (uint32).
-size_t pt_scratch_bytes(uint64_t pool_pages)
-{
-    const uint64_t nblocks = (pool_pages + kPtBlockPages - 1) / kPtBlockPages;
-    return 256 + nblocks * sizeof(uint64_t) + nblocks * sizeof(uint32_t);
-}
+// Scratch of one build: a count per workgroup of the counting pass.
+size_t pt_scratch_bytes() { return kPtMaxChunks * sizeof(uint32_t); }
 
 // The no-allocation build's scratch: a fixed block of the library's own
-// device memory (one per device, held until the process ends) for pools of
-// up to kNoAllocMaxPages pages.  Host code never passes the array's name to
-// a kernel (in host code it is only a stand-in): it uses the device address
-// that noalloc_scratch_init looks up once per context, with the context's
-// device current.
+// device memory (one per device, held until the process ends).  Host code
+// never passes the array's name to a kernel (in host code it is only a
+// stand-in): it uses the device address that noalloc_scratch_init looks up
+// once per context, with the context's device current.
 constexpr uint64_t kNoAllocMaxPages = 1ull << 26;
-constexpr size_t kNoAllocScratch = 256 + (kNoAllocMaxPages / kPtBlockPages) * 12u;  // 192.25 KiB
-static __device__ __align__(256) uint8_t scratch[kNoAllocScratch];
+static __device__ __align__(256) uint32_t scratch[kPtMaxChunks];
 
 int noalloc_scratch_init(Ctx *c)
 {
@@ -595,46 +764,150 @@ int noalloc_scratch_init(Ctx *c)
     return SGDRC_OK;
 }
 
-// Enqueues the ordered compaction shared by both page tests (counting pass,
-// scan, emitting pass: ``launch``) on ``s`` with the scratch at ``base``; the
-// count of qualifying pages goes to *d_total.
-template <class Launch>
-static int enqueue_pagetable(uint64_t pool_pages, const sgdrc_colour_set *set, void *base,
-                             uint64_t *d_total, hipStream_t s, Launch launch)
+static SetArgs set_args(const sgdrc_colour_set &set)
 {
-    const uint64_t nblocks = (pool_pages + kPtBlockPages - 1) / kPtBlockPages;
-    uint8_t *b = static_cast<uint8_t *>(base);
-    uint64_t *d_offsets = reinterpret_cast<uint64_t *>(b + 256);
-    uint32_t *d_counts = reinterpret_cast<uint32_t *>(b + 256 + nblocks * sizeof(uint64_t));
     SetArgs sa;
     for (int i = 0; i < 4; ++i) {
-        sa.w[2 * i] = (uint32_t)set->bits[i];
-        sa.w[2 * i + 1] = (uint32_t)(set->bits[i] >> 32);
+        sa.w[2 * i] = (uint32_t)set.bits[i];
+        sa.w[2 * i + 1] = (uint32_t)(set.bits[i] >> 32);
     }
-    return launch(sa, nblocks, d_counts, d_offsets, d_total, s);
+    return sa;
 }
 
-// The synchronous build: the context's scratch (allocated at init for the
-// largest pool), then the count back to the host.
+// The one-launch build of an XOR hash: whether it applies, and its constants.
+// counts[j][c] is the number of the 2^j page numbers r < 2^j with
+// c ^ colour(r) in the set, colour(r) the XOR of v[b] over r's bits b (v[b] =
+// the colour of address bit shift + b): counts[j + 1][c] = counts[j][c] +
+// counts[j][c ^ v[j]].  An aligned run of 2^m pages whose first page has
+// colour c holds counts[m][c] qualifying pages; the build applies when that
+// is the same for every c.  It is whenever the masks have full rank on the
+// m lowest page-number bits (all colours then occur equally often), as masks
+// that interleave the colours over neighbouring pages do; a hash that only
+// selects higher bits takes the general build.
+struct PtRuns {
+    uint32_t rounds = 0;      // rounds of 1024 pages per run
+    uint32_t per_run = 0;     // qualifying pages per run
+    uint32_t skip = 0;        // of the first run, before the pool's first page
+    uint32_t v0 = 0, v1 = 0;  // the colours of page-number bits 0 and 1
+    uint64_t total = 0;       // qualifying pages of the pool
+};
+
+static bool plan_runs(const sgdrc_hash *h, uint32_t page_shift, uint64_t q0, uint64_t pool_pages,
+                      const sgdrc_colour_set &set, PtRuns *out)
+{
+    constexpr uint32_t kMaxLog = 12;  // runs of 2^10..2^12 pages: one to four rounds
+    const uint32_t n = 1u << h->n_masks;
+    uint16_t counts[kMaxLog + 1][256];
+    uint32_t v[48] = {};
+    for (uint32_t b = 0; page_shift + b < 48u; ++b)
+        for (uint32_t k = 0; k < h->n_masks; ++k)
+            v[b] |= (uint32_t)((h->masks[k] >> (page_shift + b)) & 1ull) << k;
+    for (uint32_t c = 0; c < n; ++c)
+        counts[0][c] = (uint16_t)((set.bits[c >> 6] >> (c & 63u)) & 1ull);
+    uint32_t m = 0;
+    bool same = false;
+    while (m < kMaxLog && !(m >= 10u && same)) {
+        same = true;
+        for (uint32_t c = 0; c < n; ++c) {
+            counts[m + 1][c] = (uint16_t)(counts[m][c] + counts[m][c ^ v[m]]);
+            same = same && counts[m + 1][c] == counts[m + 1][0];
+        }
+        ++m;
+    }
+    if (!same)
+        return false;
+    const uint64_t run = 1ull << m;
+    // qualifying pages of x's run before x
+    auto within = [&](uint64_t x) {
+        uint32_t c = 0, f = 0;
+        for (uint32_t b = m; b < 48u - page_shift; ++b)
+            c ^= (x >> b) & 1u ? v[b] : 0u;
+        for (uint32_t b = m; b-- > 0;)
+            if ((x >> b) & 1u) {
+                f += counts[b][c];
+                c ^= v[b];
+            }
+        return f;
+    };
+    const uint64_t q1 = q0 + pool_pages;
+    out->rounds = 1u << (m - 10u);
+    out->per_run = counts[m][0];
+    out->skip = within(q0);
+    out->v0 = v[0];
+    out->v1 = v[1];
+    out->total = (q1 / run - q0 / run) * out->per_run + within(q1) - out->skip;
+    return true;
+}
+
+template <int K>
+static int launch_runs(const HashArgs &h, const PtRuns &r, uint64_t q0, uint32_t shift,
+                       uint64_t pool_pages, const SetArgs &set, uint64_t n_needed, uint32_t *d_pt,
+                       uint64_t *d_total, hipStream_t s)
+{
+    // only the runs that hold the first n_needed qualifying pages
+    const uint64_t run = 1024ull * r.rounds;
+    const uint64_t runs = (q0 + pool_pages - 1) / run - q0 / run + 1;
+    const uint64_t want = std::min(n_needed, r.total);
+    const uint64_t grid = want ? std::min(runs, (want + r.skip + r.per_run - 1) / r.per_run) : d_total ? 1 : 0;
+    if (!grid)
+        return SGDRC_OK;
+    hipLaunchKernelGGL((k_pt_runs<K>), dim3((uint32_t)grid), dim3(kPtThreads), 0, s, h, q0, shift,
+                       pool_pages, set, r.rounds, r.per_run, r.skip, r.v0, r.v1, d_pt, want,
+                       r.total, d_total);
+    SGDRC_HIP(hipGetLastError());
+    return SGDRC_OK;
+}
+
+// The general build: counting pass into ``d_counts``, emitting pass; the
+// count of qualifying pages goes to *d_total (device or pinned host memory).
+template <class Q>
+static int launch_general(const Q &q, uint32_t pages, uint64_t origin, uint32_t shift,
+                          uint64_t pool_pages, const SetArgs &set, uint64_t n_needed,
+                          uint32_t *d_pt, uint32_t *d_counts, uint64_t *d_total, hipStream_t s)
+{
+    const uint64_t round = (uint64_t)kPtThreads * pages;  // ``pages``: q.pages()
+    const uint64_t rounds = (pool_pages + round - 1) / round;
+    const uint64_t chunk = (rounds + kPtMaxChunks - 1) / kPtMaxChunks * round;
+    const uint32_t n_chunks = (uint32_t)((pool_pages + chunk - 1) / chunk);
+    hipLaunchKernelGGL((k_pt_count<Q>), dim3(n_chunks), dim3(kPtThreads), 0, s, q, origin, shift,
+                       pool_pages, chunk, set, d_counts);
+    SGDRC_HIP(hipGetLastError());
+    hipLaunchKernelGGL((k_pt_emit<Q>), dim3(n_needed ? n_chunks : 1), dim3(kPtThreads), 0, s, q,
+                       origin, shift, pool_pages, chunk, set, (const uint32_t *)d_counts, n_chunks,
+                       d_pt, n_needed, d_total);
+    SGDRC_HIP(hipGetLastError());
+    return SGDRC_OK;
+}
+
+template <int K>
+static int launch_general_xor(const HashArgs &h, uint64_t origin, uint32_t shift,
+                              uint64_t pool_pages, const SetArgs &set, uint64_t n_needed,
+                              uint32_t *d_pt, uint32_t *d_counts, uint64_t *d_total, hipStream_t s)
+{
+    return launch_general(QXor<K>{h}, QXor<K>::kPages, origin, shift, pool_pages, set, n_needed, d_pt, d_counts,
+                          d_total, s);
+}
+
+static int found_or_short(uint64_t found, uint64_t n_needed, uint64_t *n_found)
+{
+    *n_found = found;
+    if (found < n_needed)
+        return set_error(SGDRC_ENOMEM, "pool holds %llu pages of the set, %llu needed",
+                         (unsigned long long)found, (unsigned long long)n_needed);
+    return SGDRC_OK;
+}
+
+// The synchronous general build: the context's scratch, the count back
+// through pinned host memory (written by the emitting pass).
 template <class Launch>
-static int build_pagetable(Ctx *c, uint64_t pool_pages, const sgdrc_colour_set *set,
-                           uint64_t n_needed, uint64_t *n_found, void *stream, Launch launch)
+static int build_general(Ctx *c, uint64_t n_needed, uint64_t *n_found, hipStream_t s, Launch launch)
 {
     std::lock_guard<std::mutex> lock(g_pt_mu);
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (c->scratch_bytes < pt_scratch_bytes(pool_pages))
-        return set_error(SGDRC_EINVAL, "pool larger than the context's page-table scratch");
-    uint64_t *d_total = static_cast<uint64_t *>(c->d_scratch);
-    int rc = enqueue_pagetable(pool_pages, set, c->d_scratch, d_total, s, launch);
+    int rc = launch(static_cast<uint32_t *>(c->d_scratch), c->h_pinned);
     if (rc)
         return rc;
-    SGDRC_HIP(hipMemcpyAsync(c->h_pinned, d_total, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     SGDRC_HIP(hipStreamSynchronize(s));
-    *n_found = c->h_pinned[0];
-    if (*n_found < n_needed)
-        return set_error(SGDRC_ENOMEM, "pool holds %llu pages of the set, %llu needed",
-                         (unsigned long long)*n_found, (unsigned long long)n_needed);
-    return SGDRC_OK;
+    return found_or_short(c->h_pinned[0], n_needed, n_found);
 }
 
 }  // namespace sgdrc
@@ -695,15 +968,23 @@ int colour_alloc_pagetable(sgdrc_ctx *ctx, const sgdrc_hash *hash, uint64_t addr
         return rc;
     const HashArgs h = hash_args(hash);
     const sgdrc_colour_set whole = page_colour_set(hash, page_shift, *set);
-    return build_pagetable(c, pool_pages, &whole, n_needed, n_found, stream,
-                           [&](const SetArgs &sa, uint64_t nblocks, uint32_t *d_counts,
-                               uint64_t *d_offsets, uint64_t *d_total, hipStream_t s) {
-                               int rc = SGDRC_OK;
-                               SGDRC_DISPATCH_K(hash->n_masks, launch_pagetable_xor, c, h,
-                                                addr_origin, page_shift, pool_pages, sa, n_needed,
-                                                d_pt, nblocks, d_counts, d_offsets, d_total, s);
-                               return rc;
-                           });
+    const SetArgs sa = set_args(whole);
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    PtRuns r;
+    if (plan_runs(hash, page_shift, addr_origin >> page_shift, pool_pages, whole, &r)) {
+        SGDRC_DISPATCH_K(hash->n_masks, launch_runs, h, r, addr_origin >> page_shift, page_shift,
+                         pool_pages, sa, n_needed, d_pt, (uint64_t *)nullptr, s);
+        if (rc)
+            return rc;
+        SGDRC_HIP(hipStreamSynchronize(s));
+        return found_or_short(r.total, n_needed, n_found);
+    }
+    return build_general(c, n_needed, n_found, s, [&](uint32_t *d_counts, uint64_t *d_total) {
+        int rc = SGDRC_OK;
+        SGDRC_DISPATCH_K(hash->n_masks, launch_general_xor, h, addr_origin, page_shift, pool_pages,
+                         sa, n_needed, d_pt, d_counts, d_total, s);
+        return rc;
+    });
 }
 
 int colour_alloc_pagetable_noalloc(sgdrc_ctx *ctx, const sgdrc_hash *hash, uint64_t addr_origin,
@@ -721,9 +1002,8 @@ int colour_alloc_pagetable_noalloc(sgdrc_ctx *ctx, const sgdrc_hash *hash, uint6
     if (reinterpret_cast<uintptr_t>(d_n_found) & 7u)
         return set_error(SGDRC_EINVAL, "d_n_found not 8-byte aligned");
     if (pool_pages > kNoAllocMaxPages)
-        return set_error(SGDRC_EINVAL, "pool_pages %llu above the %llu pages the fixed scratch "
-                         "serves", (unsigned long long)pool_pages,
-                         (unsigned long long)kNoAllocMaxPages);
+        return set_error(SGDRC_EINVAL, "pool_pages %llu above the %llu pages this build serves",
+                         (unsigned long long)pool_pages, (unsigned long long)kNoAllocMaxPages);
     if ((rc = check_set(set, 1u << hash->n_masks)))
         return rc;
     Ctx *c = nullptr;
@@ -731,17 +1011,18 @@ int colour_alloc_pagetable_noalloc(sgdrc_ctx *ctx, const sgdrc_hash *hash, uint6
         return rc;
     const HashArgs h = hash_args(hash);
     const sgdrc_colour_set whole = page_colour_set(hash, page_shift, *set);
-    return enqueue_pagetable(pool_pages, &whole, c->d_static_scratch, d_n_found,
-                             reinterpret_cast<hipStream_t>(stream),
-                             [&](const SetArgs &sa, uint64_t nblocks, uint32_t *d_counts,
-                                 uint64_t *d_offsets, uint64_t *d_total, hipStream_t s) {
-                                 int rc = SGDRC_OK;
-                                 SGDRC_DISPATCH_K(hash->n_masks, launch_pagetable_xor, c, h,
-                                                  addr_origin, page_shift, pool_pages, sa,
-                                                  n_needed, d_pt, nblocks, d_counts, d_offsets,
-                                                  d_total, s);
-                                 return rc;
-                             });
+    const SetArgs sa = set_args(whole);
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    PtRuns r;
+    if (plan_runs(hash, page_shift, addr_origin >> page_shift, pool_pages, whole, &r)) {
+        SGDRC_DISPATCH_K(hash->n_masks, launch_runs, h, r, addr_origin >> page_shift, page_shift,
+                         pool_pages, sa, n_needed, d_pt, d_n_found, s);
+    } else {
+        SGDRC_DISPATCH_K(hash->n_masks, launch_general_xor, h, addr_origin, page_shift, pool_pages,
+                         sa, n_needed, d_pt, static_cast<uint32_t *>(c->d_static_scratch),
+                         d_n_found, s);
+    }
+    return rc;
 }
 
 int colour_classify_table(sgdrc_ctx *ctx, const sgdrc_colour_table *table,
@@ -781,14 +1062,21 @@ int colour_alloc_pagetable_table(sgdrc_ctx *ctx, const sgdrc_colour_table *table
     Ctx *c = nullptr;
     if ((rc = check_ctx(ctx, &c)))
         return rc;
-    const QTable q{TableArgs{table->lut, table->origin, table->entries, table->shift}, page_shift};
-    return build_pagetable(c, pool_pages, set, n_needed, n_found, stream,
-                           [&](const SetArgs &sa, uint64_t nblocks, uint32_t *d_counts,
-                               uint64_t *d_offsets, uint64_t *d_total, hipStream_t s) {
-                               return launch_pagetable(c, q, addr_origin, page_shift, pool_pages,
-                                                       sa, n_needed, d_pt, nblocks, d_counts,
-                                                       d_offsets, d_total, s);
-                           });
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    const TableArgs t{table->lut, table->origin, table->entries, table->shift};
+    // a page is 1 to 16 whole partitions, counted from a partition's start
+    const bool aligned = page_shift >= table->shift && page_shift <= table->shift + 4u &&
+                         ((addr_origin - table->origin) & ((1ull << table->shift) - 1ull)) == 0u;
+    return build_general(c, n_needed, n_found, s, [&](uint32_t *d_counts, uint64_t *d_total) {
+        const SetArgs sa = set_args(*set);
+        if (aligned) {
+            const uint32_t lp = page_shift - table->shift;
+            return launch_general(QTable<true>{t, lp}, 16u >> lp, addr_origin, page_shift,
+                                  pool_pages, sa, n_needed, d_pt, d_counts, d_total, s);
+        }
+        return launch_general(QTable<false>{t, 0u}, 1u, addr_origin, page_shift, pool_pages, sa,
+                              n_needed, d_pt, d_counts, d_total, s);
+    });
 }
 
 }  // extern "C"

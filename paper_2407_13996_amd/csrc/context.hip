@@ -499,10 +499,9 @@ int sgdrc_init(int device, sgdrc_ctx **out)
     TRY(hipMalloc(&c->d_err, sizeof(uint32_t)));
     TRY(hipMemset(c->d_err, 0, sizeof(uint32_t)));
     TRY(hipHostMalloc(&c->h_pinned, 8 * sizeof(uint64_t), hipHostMallocDefault));
-    // the page-table build's scratch for the largest pool (2^32 pages): a
-    // build never allocates, so it never waits for the whole device
-    c->scratch_bytes = pt_scratch_bytes(1ull << 32);
-    TRY(hipMalloc(&c->d_scratch, c->scratch_bytes));
+    // the page-table build's scratch: a build never allocates, so it never
+    // waits for the whole device
+    TRY(hipMalloc(&c->d_scratch, pt_scratch_bytes()));
 #undef TRY
     rc = noalloc_scratch_init(c);
     if (rc) {

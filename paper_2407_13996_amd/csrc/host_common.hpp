@@ -81,8 +81,7 @@ struct Ctx {
     uint64_t *d_hist_acc = nullptr;      // kMaxStreams x kHistAccCopies x kHistBins
     uint32_t *d_err = nullptr;           // one word
 
-    void *d_scratch = nullptr;           // page-table build scratch, sized for the largest pool
-    size_t scratch_bytes = 0;
+    void *d_scratch = nullptr;           // page-table build scratch
     void *d_static_scratch = nullptr;    // the device address of the no-allocation build's
                                          // scratch (a static device array of colour.hip)
     uint64_t *h_pinned = nullptr;        // 8 words of pinned host memory
@@ -101,8 +100,8 @@ struct Ctx {
 // all kMaxStreams are taken.  Caller holds c->mu.
 int take_slot(Ctx *c);
 
-// Page-table build scratch for a pool of ``pool_pages`` pages (colour.hip).
-size_t pt_scratch_bytes(uint64_t pool_pages);
+// Page-table build scratch, for any pool (colour.hip).
+size_t pt_scratch_bytes();
 
 // Looks up the device address of the no-allocation page-table build's
 // static scratch on the current device and records it in ``c`` (colour.hip;
