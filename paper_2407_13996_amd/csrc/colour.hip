@@ -69,18 +69,23 @@ struct TableArgs {
     uint32_t shift;
 };
 
+// (An address outside the table reads entry 0 and ignores it, so that no
+// branch separates a lane's gathers and all of them are in flight at once;
+// the host gives an empty table one readable byte.)
 __device__ __forceinline__ uint32_t table_colour(const TableArgs &t, uint64_t a)
 {
     const uint64_t i = (a - t.origin) >> t.shift;
     const bool in = a >= t.origin && i < t.entries;
-    return in ? (uint32_t)t.lut[in ? i : 0u] : 255u;
+    const uint32_t c = t.lut[in ? i : 0u];
+    return in ? c : 255u;
 }
 
 constexpr int kClsThreads = 256;
 constexpr int kClsLoads = 8;                             // 16-byte loads per lane per tile
-constexpr uint32_t kClsWaveTile = 64u * 2u * kClsLoads;  // 1024 addresses per wavefront
+// addresses per wavefront tile: 1024 (4096 with kPhasedLoads)
+constexpr uint32_t cls_wave_tile(int loads) { return 64u * 2u * (uint32_t)loads; }
 constexpr uint32_t kClsWaves = kClsThreads / 64;
-// Each wavefront takes its own tiles of kClsWaveTile addresses; under a mask
+// Each wavefront takes its own tiles of addresses; under a mask
 // of whole XCDs by the static schedule, otherwise through work queues of 8
 // CUs (one device-wide counter serialises its atomics at about 12 ns each).
 constexpr int kClsGroupCus = 8;
@@ -89,14 +94,38 @@ constexpr int kClsGroupCus = 8;
 // workgroup with 16 or 32 loads, or three with 8.
 constexpr int kClsWgsPerCu = 2;
 constexpr int kClsHistWgsPerCu = 2;
+// Colour tables: six workgroups per CU, whose gathers hide each other's
+// round trips when the table sits in the caches (2^24 addresses, 1024
+// entries: 30 us against 35 with two); above that the gathers' cache lines
+// bound the kernel and the number makes no difference.
+constexpr int kClsTableWgsPerCu = 6;
+
+// Colour tables larger than an XCD's 4 MiB L2: the gathers of a plain pass
+// miss it, and every miss moves a 128-byte line for one byte (2^24 addresses
+// in a 16 MiB table: 13.7 M lines, 7.5 TB/s, 235 us however many wavefronts
+// are in flight).  So each wavefront holds 4096 addresses as table indices in
+// registers and gathers them one 2 MiB slice of the table after the other:
+// the wavefronts of an XCD start together and keep step (one that runs ahead
+// waits for the misses that those behind it then hit), so a slice's lines
+// are fetched about once per XCD while all of them use it.  2^24 addresses on
+// MI355X, plain / by slices: 8 MiB table 165 / 104 us, 16 MiB 235 / 123, 64
+// MiB 308 / 214; with 1024 addresses per wavefront 182 us for 16 MiB, with
+// 1 MiB slices 127 us; a 4 MiB table 91 / 94 us.
+constexpr int kPhasedLoads = 32;
+constexpr uint32_t kPhasedGroup = 16;  // gathers in flight per lane
+constexpr uint32_t kSliceShift = 21;
+constexpr int kPhasedWgsPerCu = 4;
 
 // Histogram bins are replicated once per lane in LDS (copy = lane), so that
 // no two lanes of a wavefront ever add to one address (bin-major, so a
 // wavefront's 64 adds to one bin fall in 64 consecutive dwords).  On
 // MI355X, 2^26 addresses with K = 6: 97.1 us of kernel span against 99.2
 // with 8, 16 or 32 copies.  16 KiB of LDS per workgroup at K = 6, 64 KiB
-// for the 256 bins of a colour table (two workgroups per CU still fit).
+// for 256 bins (two workgroups per CU still fit).  The table kernels take 16
+// copies: they are bound by their gathers, and the shorter flush is worth
+// more (2^24 addresses in a 64 KiB table: 59 against 65 us).
 constexpr int kHistCopies = 64;
+constexpr int kHistTableCopies = 16;
 
 // hist_out[b] = the sum of bin b over the kHistAccCopies accumulator copies,
 // which are cleared for the next launch (every thread of one workgroup).
@@ -116,47 +145,94 @@ __device__ __forceinline__ void publish_histogram(uint64_t *hist_acc, uint64_t *
     }
 }
 
-// TAB: colours come from a colour table in device memory (one gathered
-// byte per address) instead of the XOR hash; K is then 8 (256 bins).
-template <int K, bool HIST, bool TAB>
-__global__ __launch_bounds__(kClsThreads) void k_classify(const uint64_t *__restrict__ addrs,
-                                                          uint64_t n, uint8_t *__restrict__ colours,
-                                                          HashArgs h, TableArgs tab,
-                                                          uint64_t *hist_acc, uint64_t *hist_out,
-                                                          uint32_t n_tiles, Gate g)
+// The table's colours of a tile's addresses, slice by slice (kSliceShift);
+// ``c`` in: table indices, or 0xFFFFFFFF for an address outside the table;
+// out: colours.  A lane whose index lies in another slice takes an offset past
+// the buffer resource, for which the hardware makes no access.  A finished
+// index is replaced by its colour with the upper bits set, which no slice
+// matches (the host keeps tables below 2^31 entries here).
+template <int N>
+__device__ __forceinline__ void gather_slices(const TableArgs &t, uint32_t (&c)[N])
 {
+    const Rsrc r = make_rsrc(t.lut, (uint32_t)t.entries);
+    const uint32_t slices = ((uint32_t)t.entries + (1u << kSliceShift) - 1u) >> kSliceShift;
+    for (uint32_t q = 0; q < slices; ++q) {
+#pragma unroll
+        for (int g = 0; g < N; g += (int)kPhasedGroup) {
+            uint32_t v[kPhasedGroup];
+#pragma unroll
+            for (int j = 0; j < (int)kPhasedGroup; ++j)
+                v[j] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(
+                    r, (c[g + j] >> kSliceShift) == q ? c[g + j] : 0xFFFFFFFFu, 0, 0);
+#pragma unroll
+            for (int j = 0; j < (int)kPhasedGroup; ++j)
+                c[g + j] = (c[g + j] >> kSliceShift) == q ? 0xFFFFFF00u | v[j] : c[g + j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        c[j] &= 0xFFu;
+}
+
+// Where colours come from: the XOR hash, or a colour table in device memory
+// (one gathered byte per address; K is then 8, 256 bins), gathered at once
+// or slice by slice.
+enum class ClsFrom { Hash, Table, Slices };
+
+template <int K, bool HIST, ClsFrom FROM, int LOADS>
+__device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uint64_t n,
+                                         uint8_t *__restrict__ colours, const HashArgs &h,
+                                         const TableArgs &tab, uint64_t *hist_acc,
+                                         uint64_t *hist_out, uint32_t n_tiles, const Gate &g)
+{
+    constexpr bool TAB = FROM != ClsFrom::Hash;
     constexpr uint32_t kBins = 1u << K;
-    __shared__ uint32_t s_hist[HIST ? kBins * kHistCopies : 1];
+    constexpr uint32_t kTile = cls_wave_tile(LOADS);
+    constexpr int kCopies = TAB ? kHistTableCopies : kHistCopies;
+    __shared__ uint32_t s_hist[HIST ? kBins * kCopies : 1];
     // per wavefront: the colour bytes of one tile, 2 per lane and load
-    __shared__ __attribute__((aligned(16))) uint16_t s_col[kClsThreads / 64][kClsWaveTile / 2];
+    __shared__ __attribute__((aligned(16))) uint16_t s_col[kClsThreads / 64][kTile / 2];
     __shared__ __attribute__((aligned(16))) uint8_t s_lut[kLutBytes][256];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t copy = lane % kHistCopies;
+    const uint32_t copy = lane % kCopies;
     const uint64_t n16 = n & ~15ull;
     if (HIST) {
-        for (uint32_t i = threadIdx.x; i < kBins * kHistCopies; i += kClsThreads)
+        for (uint32_t i = threadIdx.x; i < kBins * kCopies; i += kClsThreads)
             s_hist[i] = 0;
         __syncthreads();
     }
     auto body = [&](uint32_t t, uint32_t, uint32_t &, auto &&claim) {
         // a tile is one wavefront's: its first address, and how many of its
         // addresses lie below n16 (a multiple of 16, possibly 0)
-        const uint64_t base = (uint64_t)t * kClsWaveTile;
-        const uint32_t valid =
-            n16 > base ? (uint32_t)(n16 - base < kClsWaveTile ? n16 - base : kClsWaveTile) : 0u;
+        const uint64_t base = (uint64_t)t * kTile;
+        const uint32_t valid = n16 > base ? (uint32_t)(n16 - base < kTile ? n16 - base : kTile) : 0u;
         const Rsrc ra = make_rsrc(addrs + base, valid * 8u);
-        u32x4 v[kClsLoads];
+        u32x4 v[LOADS];
 #pragma unroll
-        for (int j = 0; j < kClsLoads; ++j)
+        for (int j = 0; j < LOADS; ++j)
             v[j] = buf_load_nt(ra, (j * 64u + lane) * 16u);
         claim();
+        uint32_t tc[TAB ? 2 * LOADS : 1];
+        if (TAB) {
 #pragma unroll
-        for (int j = 0; j < kClsLoads; ++j) {
-            const uint32_t c0 = TAB ? table_colour(tab, ((uint64_t)v[j].y << 32) | v[j].x)
-                                    : colour_lut(s_lut, v[j].x, v[j].y);
-            const uint32_t c1 = TAB ? table_colour(tab, ((uint64_t)v[j].w << 32) | v[j].z)
-                                    : colour_lut(s_lut, v[j].z, v[j].w);
+            for (int j = 0; j < 2 * LOADS; ++j) {
+                const u32x4 &w = v[j / 2];
+                const uint64_t a = j & 1 ? ((uint64_t)w.w << 32) | w.z : ((uint64_t)w.y << 32) | w.x;
+                if (FROM == ClsFrom::Table) {
+                    tc[TAB ? j : 0] = table_colour(tab, a);
+                } else {
+                    const uint64_t i = (a - tab.origin) >> tab.shift;
+                    tc[TAB ? j : 0] = a >= tab.origin && i < tab.entries ? (uint32_t)i : 0xFFFFFFFFu;
+                }
+            }
+            if constexpr (FROM == ClsFrom::Slices)
+                gather_slices<2 * LOADS>(tab, tc);
+        }
+#pragma unroll
+        for (int j = 0; j < LOADS; ++j) {
+            const uint32_t c0 = TAB ? tc[TAB ? 2 * j : 0] : colour_lut(s_lut, v[j].x, v[j].y);
+            const uint32_t c1 = TAB ? tc[TAB ? 2 * j + 1 : 0] : colour_lut(s_lut, v[j].z, v[j].w);
             s_col[wave][j * 64u + lane] = (uint16_t)(c0 | (c1 << 8));
             // both addresses of the load are valid or neither (valid is even);
             // invalid ones (read as address 0, a bin in range) add 0, so
@@ -164,21 +240,21 @@ __global__ __launch_bounds__(kClsThreads) void k_classify(const uint64_t *__rest
             // the histogram cost several microseconds more)
             if (HIST) {
                 const uint32_t inc = 2u * (j * 64u + lane) < valid ? 1u : 0u;
-                atomicAdd(&s_hist[c0 * kHistCopies + copy], inc);
-                atomicAdd(&s_hist[c1 * kHistCopies + copy], inc);
+                atomicAdd(&s_hist[c0 * kCopies + copy], inc);
+                atomicAdd(&s_hist[c1 * kCopies + copy], inc);
             }
         }
         // LDS accesses of one wavefront complete in order; the wave
         // barriers only keep the compiler from moving these accesses
         __builtin_amdgcn_wave_barrier();
-        u32x4 out[kClsLoads / 8];
+        u32x4 out[LOADS / 8];
 #pragma unroll
-        for (int q = 0; q < kClsLoads / 8; ++q)
+        for (int q = 0; q < LOADS / 8; ++q)
             out[q] = *reinterpret_cast<const u32x4 *>(&s_col[wave][q * 512u + lane * 8u]);
         __builtin_amdgcn_wave_barrier();
         const Rsrc rc = make_rsrc(colours + base, valid);
 #pragma unroll
-        for (int q = 0; q < kClsLoads / 8; ++q)
+        for (int q = 0; q < LOADS / 8; ++q)
             buf_store_sc1(rc, q * 1024u + lane * 16u, out[q]);
     };
     auto flush = [&]() {
@@ -190,9 +266,9 @@ __global__ __launch_bounds__(kClsThreads) void k_classify(const uint64_t *__rest
             for (uint32_t b = threadIdx.x; b < kBins; b += kClsThreads) {
                 uint32_t v = 0;
 #pragma unroll
-                for (int r = 0; r < kHistCopies; ++r) {
-                    v += s_hist[b * kHistCopies + r];
-                    s_hist[b * kHistCopies + r] = 0;
+                for (int r = 0; r < kCopies; ++r) {
+                    v += s_hist[b * kCopies + r];
+                    s_hist[b * kCopies + r] = 0;
                 }
                 if (v)
                     __hip_atomic_fetch_add(&acc[b], (uint64_t)v, __ATOMIC_RELAXED,
@@ -236,6 +312,30 @@ __global__ __launch_bounds__(kClsThreads) void k_classify(const uint64_t *__rest
         static_wave_loop(g, n_tiles, prologue, body, flush);
     else
         gated_wave_loop(g, n_tiles, prologue, body, flush, epilogue);
+}
+
+template <int K, bool HIST, bool TAB>
+__global__ __launch_bounds__(kClsThreads) void k_classify(const uint64_t *__restrict__ addrs,
+                                                          uint64_t n, uint8_t *__restrict__ colours,
+                                                          HashArgs h, TableArgs tab,
+                                                          uint64_t *hist_acc, uint64_t *hist_out,
+                                                          uint32_t n_tiles, Gate g)
+{
+    classify<K, HIST, TAB ? ClsFrom::Table : ClsFrom::Hash, kClsLoads>(addrs, n, colours, h, tab,
+                                                                       hist_acc, hist_out, n_tiles, g);
+}
+
+template <bool HIST>
+__global__ __launch_bounds__(kClsThreads) void k_classify_slices(const uint64_t *__restrict__ addrs,
+                                                                 uint64_t n,
+                                                                 uint8_t *__restrict__ colours,
+                                                                 HashArgs h, TableArgs tab,
+                                                                 uint64_t *hist_acc,
+                                                                 uint64_t *hist_out,
+                                                                 uint32_t n_tiles, Gate g)
+{
+    classify<8, HIST, ClsFrom::Slices, kPhasedLoads>(addrs, n, colours, h, tab, hist_acc, hist_out,
+                                                     n_tiles, g);
 }
 
 // After a statically scheduled classify (one workgroup, stream-ordered
@@ -597,13 +697,31 @@ static HashArgs hash_args(const sgdrc_hash *h)
     return a;
 }
 
+// Whether a table is gathered slice by slice: larger than an XCD's L2, few
+// enough slices (each costs the wavefronts an instruction per index; measured
+// up to 32), and enough addresses that a line fetched by an XCD is used
+// several times (n / 8 addresses per XCD against entries / 128 lines) and all
+// wavefronts have a tile.  Plain / by slices on MI355X: 2^22 addresses, 8 MiB
+// 45 / 32 us, 16 MiB 62 / 37; 2^21 addresses, 8 MiB 25 / 31 us.
+static bool gather_by_slices(const TableArgs &t, uint64_t n)
+{
+    return t.entries > (2ull << kSliceShift) && t.entries <= (32ull << kSliceShift) &&
+           n >= t.entries / 4u && n >= (1ull << 22);
+}
+
+typedef void (*ClassifyKernel)(const uint64_t *, uint64_t, uint8_t *, HashArgs, TableArgs,
+                               uint64_t *, uint64_t *, uint32_t, Gate);
+
 template <int K, bool TAB>
 static int launch_classify(Ctx *c, const HashArgs &h, const TableArgs &tab,
                            const uint64_t *d_addrs, uint64_t n, uint8_t *d_colours,
                            uint64_t *d_hist, void *stream)
 {
-    const uint64_t n_tiles = ((n & ~15ull) + kClsWaveTile - 1) / kClsWaveTile;
-    if (n_tiles >= (1ull << 31))
+    const bool slices = TAB && gather_by_slices(tab, n);
+    const uint32_t tile = cls_wave_tile(slices ? kPhasedLoads : kClsLoads);
+    const uint64_t n_tiles = ((n & ~15ull) + tile - 1) / tile;
+    // (the bound of 1024-address tiles, whatever the tile)
+    if (n / cls_wave_tile(kClsLoads) >= (1ull << 31) - 1u)
         return set_error(SGDRC_EINVAL, "n too large");
     // grid sizing counts workgroups' worth of tiles
     const uint64_t wg_tiles = (n_tiles + kClsWaves - 1) / kClsWaves;
@@ -614,17 +732,23 @@ static int launch_classify(Ctx *c, const HashArgs &h, const TableArgs &tab,
         return rc;
     uint64_t *acc = c->d_hist_acc + (size_t)(g.q - c->d_queues) * kHistAccCopies * kHistBins;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (d_hist) {
-        static const int occ = occupancy(k_classify<K, true, TAB>, kClsThreads);
-        uint32_t grid = gated_grid(c, std::min(occ, kClsHistWgsPerCu), wg_tiles, li);
-        hipLaunchKernelGGL((k_classify<K, true, TAB>), dim3(grid), dim3(kClsThreads), 0, s,
-                           d_addrs, n, d_colours, h, tab, acc, d_hist, (uint32_t)n_tiles, g);
+    ClassifyKernel k = d_hist ? k_classify<K, true, TAB> : k_classify<K, false, TAB>;
+    int per_cu = d_hist ? kClsHistWgsPerCu : kClsWgsPerCu;
+    if constexpr (TAB) {
+        static const int occ[2][2] = {{occupancy(k_classify<K, false, true>, kClsThreads),
+                                       occupancy(k_classify<K, true, true>, kClsThreads)},
+                                      {occupancy(k_classify_slices<false>, kClsThreads),
+                                       occupancy(k_classify_slices<true>, kClsThreads)}};
+        if (slices)
+            k = d_hist ? k_classify_slices<true> : k_classify_slices<false>;
+        per_cu = std::min(occ[slices][d_hist != nullptr], slices ? kPhasedWgsPerCu : kClsTableWgsPerCu);
     } else {
-        static const int occ = occupancy(k_classify<K, false, TAB>, kClsThreads);
-        uint32_t grid = gated_grid(c, std::min(occ, kClsWgsPerCu), wg_tiles, li);
-        hipLaunchKernelGGL((k_classify<K, false, TAB>), dim3(grid), dim3(kClsThreads), 0, s,
-                           d_addrs, n, d_colours, h, tab, acc, d_hist, (uint32_t)n_tiles, g);
+        static const int occ[2] = {occupancy(k_classify<K, false, false>, kClsThreads),
+                                   occupancy(k_classify<K, true, false>, kClsThreads)};
+        per_cu = std::min(occ[d_hist != nullptr], per_cu);
     }
+    hipLaunchKernelGGL(k, dim3(gated_grid(c, per_cu, wg_tiles, li)), dim3(kClsThreads), 0, s,
+                       d_addrs, n, d_colours, h, tab, acc, d_hist, (uint32_t)n_tiles, g);
     SGDRC_HIP(hipGetLastError());
     if (g.statics) {
         // the statically scheduled grid has no last workgroup: the tail and
@@ -1042,7 +1166,9 @@ int colour_classify_table(sgdrc_ctx *ctx, const sgdrc_colour_table *table,
     Ctx *c = nullptr;
     if ((rc = check_ctx(ctx, &c)))
         return rc;
-    const TableArgs t{table->lut, table->origin, table->entries, table->shift};
+    // (an empty table: any readable byte, see table_colour)
+    const uint8_t *lut = table->entries ? table->lut : reinterpret_cast<const uint8_t *>(c->d_lut);
+    const TableArgs t{lut, table->origin, table->entries, table->shift};
     return launch_classify<8, true>(c, HashArgs{}, t, d_addrs, n, d_colours, d_hist, stream);
 }
 
