@@ -96,6 +96,34 @@ static uint32_t xcc_allowed(const Ctx *c, const sgdrc_cu_mask &m)
     return bits;
 }
 
+// The rank of each XCC_ID among the XCDs that ``m`` allows (0xFF: not
+// allowed) and their number, or 0 when an XCD is allowed in part.
+static uint32_t whole_xcds(const Ctx *c, const sgdrc_cu_mask &m, uint8_t rank[kMaxXcds])
+{
+    std::memset(rank, 0xFF, kMaxXcds);
+    uint32_t a = 0;
+    for (int x = 0; x < c->n_xcds; ++x) {
+        int on = 0;
+        const int first = c->xcd_first_cu[x], count = c->xcd_first_cu[x + 1] - first;
+        for (int cu = first; cu < first + count; ++cu)
+            on += (int)((m.bits[cu >> 6] >> (cu & 63)) & 1ull);
+        if (on == count)
+            rank[(c->keys[first] >> 8) & 0xFu] = (uint8_t)a++;
+        else if (on != 0)
+            return 0;
+    }
+    return a;
+}
+
+int static_cus(Ctx *c, void *stream)
+{
+    std::lock_guard<std::mutex> lock(c->mu);
+    auto it = c->streams.find(stream);
+    const sgdrc_cu_mask &m = it != c->streams.end() ? it->second.mask : c->all_cus;
+    uint8_t rank[kMaxXcds];
+    return c->static_ok && whole_xcds(c, m, rank) ? popcount_mask(m) : 0;
+}
+
 int make_gate(Ctx *c, void *stream, uint64_t n_tiles, int group_cus, Gate *g, LaunchInfo *li,
               bool preemptible, bool allow_static)
 {
@@ -171,21 +199,9 @@ int make_gate(Ctx *c, void *stream, uint64_t n_tiles, int group_cus, Gate *g, La
     g->n_allowed_xcd = 0u;
     g->n_xcd = (uint32_t)c->n_xcds;
     if (allow_static && !preemptible && c->static_ok) {
-        bool whole = true;
         uint8_t rank[kMaxXcds];
-        std::memset(rank, 0xFF, sizeof rank);
-        uint32_t a = 0;
-        for (int x = 0; x < c->n_xcds && whole; ++x) {
-            int on = 0;
-            const int first = c->xcd_first_cu[x], count = c->xcd_first_cu[x + 1] - first;
-            for (int cu = first; cu < first + count; ++cu)
-                on += (int)((st->mask.bits[cu >> 6] >> (cu & 63)) & 1ull);
-            if (on == count)
-                rank[(c->keys[first] >> 8) & 0xFu] = (uint8_t)a++;
-            else if (on != 0)
-                whole = false;
-        }
-        if (whole && a > 0) {
+        const uint32_t a = whole_xcds(c, st->mask, rank);
+        if (a > 0) {
             g->statics = 1u;
             std::memcpy(g->xcd_rank, rank, sizeof rank);
             g->n_allowed_xcd = a;

@@ -617,10 +617,11 @@ __device__ __forceinline__ void gated_tile_loop(const Gate &g, uint32_t n_tiles,
 // its stores are done, raises partial end stamp blockIdx mod kTimePartials
 // to its end time; the host reduces the partials with k_tlog_reduce after
 // the launch.  ``prologue`` and ``body`` as in gated_tile_loop (``claim`` has
-// no effect).
-template <typename Prologue, typename Body>
+// no effect); ``tail``, work that needs no other tile's result, runs once, in
+// worker 0 after its tiles.
+template <typename Prologue, typename Body, typename Tail = NoOp>
 __device__ __forceinline__ void static_tile_loop(const Gate &g, uint32_t n_tiles, Prologue prologue,
-                                                 Body body)
+                                                 Body body, Tail tail = Tail())
 {
     uint32_t xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
@@ -639,6 +640,8 @@ __device__ __forceinline__ void static_tile_loop(const Gate &g, uint32_t n_tiles
             log_tile(g, cu, t);
             body(t, cu, err, NoOp());
         }
+        if (a == 0u && blockIdx.x < g.n_xcd)
+            tail();
     }
     if (g.tlog) {
         __builtin_amdgcn_s_waitcnt(0);

@@ -140,6 +140,10 @@ int make_gate(Ctx *c, void *stream, uint64_t n_tiles, int group_cus, Gate *g, La
 // the log slot (k_tlog_reduce).
 int finish_static_tlog(const Gate &g, hipStream_t s);
 
+// CUs that the stream's mask allows if launches on it may take the static
+// schedule (a mask of whole XCDs), else 0.
+int static_cus(Ctx *c, void *stream);
+
 // CUs that the stream's mask allows (all CUs for a stream not seen yet).
 int stream_allowed_cus(Ctx *c, void *stream);
 

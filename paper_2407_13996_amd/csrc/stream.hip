@@ -1,12 +1,14 @@
 // Page-table-indirected streaming kernels: bimodal relayout (page-set to
 // page-set copy) and the colour-restricted triad a = b + s*c.
 //
-// Both run as gated persistent grids over a tile queue, one workgroup per
-// CU.  A tile is 64 KiB of logical bytes per array; each of the four
-// wavefronts of a workgroup owns 16 KiB of it, and every lane moves 16
-// chunks of 16 bytes (256 bytes in flight per lane and array) with
-// non-temporal buffer loads and stores, each wavefront instruction covering
-// 1 KiB of consecutive bytes.
+// Both run as gated persistent grids, one workgroup per CU.  A tile is 64 KiB
+// of logical bytes per array; each of the four wavefronts of a workgroup owns
+// 16 KiB of it, and every lane moves 16 chunks of 16 bytes (256 bytes in
+// flight per lane and array) with non-temporal buffer loads and stores, each
+// wavefront instruction covering 1 KiB of consecutive bytes.  Short launches
+// on masks of whole XCDs take their tiles by the static schedule, and the
+// shortest use tiles of 16 KiB (stream_plan); other launches take tiles from
+// the queue.
 //
 // The tile's page-table entries (one to sixteen pages) are staged in LDS.
 // Every 1 KiB wavefront chunk lies inside one page, and each gets its own
@@ -24,7 +26,7 @@
 //
 // Tiles cover the largest multiple of 16 bytes; the last n_bytes mod 16
 // bytes are moved by the last workgroup of the grid after all tiles are
-// done (it may sit on any CU).
+// done (it may sit on any CU), or by the first worker of a static launch.
 #include "host_common.hpp"
 
 namespace sgdrc {
@@ -52,6 +54,11 @@ constexpr int kTriadUnroll = 16;
 constexpr int kTriadUnrollEv = 16;
 constexpr int kRelayoutUnroll = 16;
 constexpr int kStreamWgsPerCu = 1;
+// The shortest launches: tiles of 16 KiB, up to four workgroups per CU.
+constexpr int kSmallUnroll = 4;
+constexpr int kSmallWgsPerCu = 4;
+// Static schedule up to this many 64 KiB tiles per CU (see stream_plan).
+constexpr uint64_t kStaticTilesPerCu = 32;
 // each workgroup of a preemptible launch hands back at most one tile
 static_assert(2 * kStreamWgsPerCu * kMaxCus <= (int)kHandBackCap, "hand-back ring too small");
 
@@ -231,7 +238,10 @@ __global__ __launch_bounds__(kStreamThreads) void k_relayout(
             }
         }
     };
-    gated_tile_loop<Claim::Mid, EV>(g, n_tiles, NoOp(), body, NoOp(), epilogue);
+    if (!EV && g.statics)
+        static_tile_loop(g, n_tiles, NoOp(), body, epilogue);
+    else
+        gated_tile_loop<Claim::Mid, EV>(g, n_tiles, NoOp(), body, NoOp(), epilogue);
 }
 
 // Several copies in one launch: the tiles of item i are [tile0_i,
@@ -274,7 +284,10 @@ __global__ __launch_bounds__(kStreamThreads) void k_relayout_batch(RelayoutBatch
                           r.shift, g.err);
         }
     };
-    gated_tile_loop<Claim::Mid>(g, n_tiles, NoOp(), body, NoOp(), epilogue);
+    if (g.statics)
+        static_tile_loop(g, n_tiles, NoOp(), body, epilogue);
+    else
+        gated_tile_loop<Claim::Mid>(g, n_tiles, NoOp(), body, NoOp(), epilogue);
 }
 
 __device__ __forceinline__ u32x4 fma4(float s, u32x4 c, u32x4 b)
@@ -350,7 +363,40 @@ __global__ __launch_bounds__(kStreamThreads) void k_triad(
             }
         }
     };
-    gated_tile_loop<Claim::Mid, EV>(g, n_tiles, NoOp(), body, NoOp(), epilogue);
+    if (!EV && g.statics)
+        static_tile_loop(g, n_tiles, NoOp(), body, epilogue);
+    else
+        gated_tile_loop<Claim::Mid, EV>(g, n_tiles, NoOp(), body, NoOp(), epilogue);
+}
+
+// How a launch over ``tiles64`` tiles of 64 KiB takes its tiles.  The queue
+// hands out one ticket per tile from one counter (about 12 ns each, so that
+// the 256 first tickets alone take 3 us) and counts arrivals at the end; the
+// static schedule has neither.  It is taken while a CU has at most
+// kStaticTilesPerCu tiles, beyond which the queue's even finish is worth as
+// much.  On MI355X, 64 KiB pages, 256 CUs, queue / static: triad of 3000001
+// elements 15.3 / 8.3 us, 33000000 73.8 / 66.0, 67000000 134.4 / 129.7,
+// 134000000 252.9 / 254.7; relayout of 32 MiB 21.4 / 13.4, 256 MiB 92.1 /
+// 86.9, 512 MiB 169.7 / 168.3, 1 GiB 331.5 / 332.8.  Preemptible launches
+// always take the queue, which their resumption continues.
+//
+// With at most one 64 KiB tile per CU, tiles of 16 KiB put more CUs to work
+// (static schedule only): triad of 3000001 elements in 2 KiB pages 9.2 / 8.5
+// us; on the queue four workgroups per CU contend for its counter (15.8 /
+// 50.6 us).
+struct StreamPlan {
+    bool statics, small;
+};
+
+static StreamPlan stream_plan(Ctx *c, void *stream, uint64_t tiles64, bool ev)
+{
+    const uint64_t cus = ev ? 0u : (uint64_t)static_cus(c, stream);
+    return {cus && tiles64 <= kStaticTilesPerCu * cus, cus && tiles64 <= cus};
+}
+
+static uint64_t tiles_of(uint64_t n_bytes, uint32_t tile)
+{
+    return ((n_bytes & ~15ull) + tile - 1) / tile;
 }
 
 }  // namespace sgdrc
@@ -372,22 +418,24 @@ int bimodal_relayout(sgdrc_ctx *ctx, const sgdrc_paged *dst, const sgdrc_paged *
     rc = check_ctx(ctx, &c);
     if (rc)
         return rc;
-    constexpr int U = kRelayoutUnroll;
-    constexpr uint32_t tile = Geo<U>::kTile;
-    const uint64_t n_tiles = ((n_bytes & ~15ull) + tile - 1) / tile;
-    if (n_tiles >= (1ull << 31))
+    constexpr int U = kRelayoutUnroll, US = kSmallUnroll;
+    const uint64_t tiles64 = tiles_of(n_bytes, Geo<U>::kTile);
+    if (tiles64 >= (1ull << 31))
         return set_error(SGDRC_EINVAL, "n_bytes too large");
     const bool ev = stream_preemptible(c, stream);
+    const StreamPlan plan = stream_plan(c, stream, tiles64, ev);
+    const uint64_t n_tiles = plan.small ? tiles_of(n_bytes, Geo<US>::kTile) : tiles64;
     if (ev && (rc = discard_suspended(c, stream)))
         return rc;
     Gate g;
     LaunchInfo li;
-    rc = make_gate(c, stream, n_tiles, kStreamGroupCus, &g, &li, ev);
+    rc = make_gate(c, stream, n_tiles, kStreamGroupCus, &g, &li, ev, plan.statics);
     if (rc)
         return rc;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     static const int occ = occupancy(k_relayout<U, false>, kStreamThreads);
-    const int per_cu = std::min(occ, kStreamWgsPerCu);
+    static const int occ_small = occupancy(k_relayout<US, false>, kStreamThreads);
+    const int per_cu = plan.small ? std::min(occ_small, kSmallWgsPerCu) : std::min(occ, kStreamWgsPerCu);
     const uint32_t grid = gated_grid(c, per_cu, n_tiles, li);
     uint8_t *const d = static_cast<uint8_t *>(dst->pool);
     const uint8_t *const sp = static_cast<const uint8_t *>(src->pool);
@@ -398,16 +446,16 @@ int bimodal_relayout(sgdrc_ctx *ctx, const sgdrc_paged *dst, const sgdrc_paged *
             hipLaunchKernelGGL((k_relayout<U, true>), dim3(gr), dim3(kStreamThreads), 0, s, d, dpt,
                                dpages, sp, spt, spages, n_bytes, page_shift, (uint32_t)n_tiles, gg);
         else
-            hipLaunchKernelGGL((k_relayout<U, false>), dim3(gr), dim3(kStreamThreads), 0, s, d,
-                               dpt, dpages, sp, spt, spages, n_bytes, page_shift,
-                               (uint32_t)n_tiles, gg);
+            hipLaunchKernelGGL((plan.small ? k_relayout<US, false> : k_relayout<U, false>), dim3(gr),
+                               dim3(kStreamThreads), 0, s, d, dpt, dpages, sp, spt, spages, n_bytes,
+                               page_shift, (uint32_t)n_tiles, gg);
         return hipGetLastError();
     };
     SGDRC_HIP(launch(g, grid, ev));
     if (ev)
         record_preemptible(c, stream, g, n_tiles, per_cu,
                            [launch](const Gate &gg, uint32_t gr) { return launch(gg, gr, true); });
-    return SGDRC_OK;
+    return finish_static_tlog(g, s);
 }
 
 int bimodal_relayout_batch(sgdrc_ctx *ctx, const sgdrc_relayout_item *items, uint32_t n_items,
@@ -416,8 +464,7 @@ int bimodal_relayout_batch(sgdrc_ctx *ctx, const sgdrc_relayout_item *items, uin
     clear_error();
     if (n_items && !items)
         return set_error(SGDRC_EINVAL, "items is NULL");
-    constexpr int U = kRelayoutUnroll;
-    constexpr uint32_t tile = Geo<U>::kTile;
+    constexpr int U = kRelayoutUnroll, US = kSmallUnroll;
     for (uint32_t i = 0; i < n_items; ++i) {
         const sgdrc_relayout_item &it = items[i];
         int rc = check_shift(it.page_shift);
@@ -428,7 +475,7 @@ int bimodal_relayout_batch(sgdrc_ctx *ctx, const sgdrc_relayout_item *items, uin
             return set_error(SGDRC_EINVAL, "item %u: %s", i, sgdrc_last_error());
         if (it.reserved != 0)
             return set_error(SGDRC_EINVAL, "item %u: reserved must be 0", i);
-        if (((it.n_bytes & ~15ull) + tile - 1) / tile >= (1ull << 31))
+        if (tiles_of(it.n_bytes, Geo<U>::kTile) >= (1ull << 31))
             return set_error(SGDRC_EINVAL, "item %u: n_bytes too large", i);
     }
     Ctx *c = nullptr;
@@ -437,9 +484,18 @@ int bimodal_relayout_batch(sgdrc_ctx *ctx, const sgdrc_relayout_item *items, uin
         return rc;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     static const int occ = occupancy(k_relayout_batch<U>, kStreamThreads);
-    const int per_cu = std::min(occ, kStreamWgsPerCu);
+    static const int occ_small = occupancy(k_relayout_batch<US>, kStreamThreads);
     for (uint32_t first = 0; first < n_items; first += kBatchItems) {
         const uint32_t n = std::min<uint32_t>(kBatchItems, n_items - first);
+        uint64_t tiles64 = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            tiles64 += tiles_of(items[first + i].n_bytes, Geo<U>::kTile);
+            if (tiles64 >= (1ull << 31))
+                return set_error(SGDRC_EINVAL, "items %u..%u: too many bytes for one launch", first,
+                                 first + i);
+        }
+        const StreamPlan plan = stream_plan(c, stream, tiles64, false);
+        const uint32_t tile = plan.small ? Geo<US>::kTile : Geo<U>::kTile;
         RelayoutBatch b{};
         uint64_t tiles = 0;
         for (uint32_t i = 0; i < n; ++i) {
@@ -454,20 +510,20 @@ int bimodal_relayout_batch(sgdrc_ctx *ctx, const sgdrc_relayout_item *items, uin
             r.n_bytes = it.n_bytes;
             r.shift = it.page_shift;
             r.tile0 = (uint32_t)tiles;
-            tiles += ((it.n_bytes & ~15ull) + tile - 1) / tile;
-            if (tiles >= (1ull << 31))
-                return set_error(SGDRC_EINVAL, "items %u..%u: too many bytes for one launch", first,
-                                 first + i);
+            tiles += tiles_of(it.n_bytes, tile);
         }
         b.n = n;
         Gate g;
         LaunchInfo li;
-        if ((rc = make_gate(c, stream, tiles, kStreamGroupCus, &g, &li, false)))
+        if ((rc = make_gate(c, stream, tiles, kStreamGroupCus, &g, &li, false, plan.statics)))
             return rc;
+        const int per_cu = plan.small ? std::min(occ_small, kSmallWgsPerCu) : std::min(occ, kStreamWgsPerCu);
         const uint32_t grid = gated_grid(c, per_cu, tiles, li);
-        hipLaunchKernelGGL((k_relayout_batch<U>), dim3(grid), dim3(kStreamThreads), 0, s, b,
-                           (uint32_t)tiles, g);
+        hipLaunchKernelGGL((plan.small ? k_relayout_batch<US> : k_relayout_batch<U>), dim3(grid),
+                           dim3(kStreamThreads), 0, s, b, (uint32_t)tiles, g);
         SGDRC_HIP(hipGetLastError());
+        if ((rc = finish_static_tlog(g, s)))
+            return rc;
     }
     return SGDRC_OK;
 }
@@ -489,22 +545,24 @@ int colored_stream(sgdrc_ctx *ctx, const sgdrc_paged *a, const sgdrc_paged *b,
     if (rc)
         return rc;
     const uint64_t n_bytes = n_elems * 4u;
-    constexpr int U = kTriadUnroll, UE = kTriadUnrollEv;
+    constexpr int U = kTriadUnroll, UE = kTriadUnrollEv, US = kSmallUnroll;
     const bool ev = stream_preemptible(c, stream);
-    const uint32_t tile = ev ? Geo<UE>::kTile : Geo<U>::kTile;
-    const uint64_t n_tiles = ((n_bytes & ~15ull) + tile - 1) / tile;
-    if (n_tiles >= (1ull << 31))
+    const uint64_t tiles64 = tiles_of(n_bytes, ev ? Geo<UE>::kTile : Geo<U>::kTile);
+    if (tiles64 >= (1ull << 31))
         return set_error(SGDRC_EINVAL, "n_elems too large");
+    const StreamPlan plan = stream_plan(c, stream, tiles64, ev);
+    const uint64_t n_tiles = plan.small ? tiles_of(n_bytes, Geo<US>::kTile) : tiles64;
     if (ev && (rc = discard_suspended(c, stream)))
         return rc;
     Gate g;
     LaunchInfo li;
-    rc = make_gate(c, stream, n_tiles, kStreamGroupCus, &g, &li, ev);
+    rc = make_gate(c, stream, n_tiles, kStreamGroupCus, &g, &li, ev, plan.statics);
     if (rc)
         return rc;
     hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
     static const int occ = occupancy(k_triad<U, false>, kStreamThreads);
-    const int per_cu = std::min(occ, kStreamWgsPerCu);
+    static const int occ_small = occupancy(k_triad<US, false>, kStreamThreads);
+    const int per_cu = plan.small ? std::min(occ_small, kSmallWgsPerCu) : std::min(occ, kStreamWgsPerCu);
     const uint32_t grid = gated_grid(c, per_cu, n_tiles, li);
     uint8_t *const ap = static_cast<uint8_t *>(a->pool);
     const uint8_t *const bp = static_cast<const uint8_t *>(b->pool);
@@ -517,16 +575,16 @@ int colored_stream(sgdrc_ctx *ctx, const sgdrc_paged *a, const sgdrc_paged *b,
                                an, bp, bpt, bn, cp, cpt, cn, s, n_bytes, page_shift,
                                (uint32_t)n_tiles, gg);
         else
-            hipLaunchKernelGGL((k_triad<U, false>), dim3(gr), dim3(kStreamThreads), 0, hs, ap, apt,
-                               an, bp, bpt, bn, cp, cpt, cn, s, n_bytes, page_shift,
-                               (uint32_t)n_tiles, gg);
+            hipLaunchKernelGGL((plan.small ? k_triad<US, false> : k_triad<U, false>), dim3(gr),
+                               dim3(kStreamThreads), 0, hs, ap, apt, an, bp, bpt, bn, cp, cpt, cn, s,
+                               n_bytes, page_shift, (uint32_t)n_tiles, gg);
         return hipGetLastError();
     };
     SGDRC_HIP(launch(g, grid, ev));
     if (ev)
         record_preemptible(c, stream, g, n_tiles, per_cu,
                            [launch](const Gate &gg, uint32_t gr) { return launch(gg, gr, true); });
-    return SGDRC_OK;
+    return finish_static_tlog(g, hs);
 }
 
 }  // extern "C"
