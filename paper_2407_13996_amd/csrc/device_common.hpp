@@ -616,33 +616,36 @@ __device__ __forceinline__ void gated_tile_loop(const Gate &g, uint32_t n_tiles,
 // With a time log, workgroup 0 stamps the start and every workgroup, once
 // its stores are done, raises partial end stamp blockIdx mod kTimePartials
 // to its end time; the host reduces the partials with k_tlog_reduce after
-// the launch.  ``prologue`` and ``body`` as in gated_tile_loop (``claim`` has
-// no effect); ``tail``, work that needs no other tile's result, runs once, in
-// worker 0 after its tiles.
-template <typename Prologue, typename Body, typename Tail = NoOp>
-__device__ __forceinline__ void static_tile_loop(const Gate &g, uint32_t n_tiles, Prologue prologue,
-                                                 Body body, Tail tail = Tail())
+// the launch.  A workgroup on an allowed XCD runs ``prime`` with its first
+// tile (for loads that need not wait for the opening barrier), every workgroup
+// runs ``prologue``, and ``body(tile, next, cu, err)`` runs for each of the
+// workgroup's tiles with the tile it takes after that (n_tiles or more: none);
+// ``tail``, work that needs no other tile's result, runs once, in worker 0
+// after its tiles.
+template <typename Prime, typename Prologue, typename Body, typename Tail>
+__device__ __forceinline__ void static_tile_stream(const Gate &g, uint32_t n_tiles, Prime prime,
+                                                   Prologue prologue, Body body, Tail tail)
 {
     uint32_t xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
     const uint32_t a = g.xcd_rank[xcc & 0xFu];
     // the work log names the logical CU: one table read, only when logging
     const uint32_t cu = g.log_cu ? (my_cu_entry(g) & 0xFFFFu) : (uint32_t)kMaxCus;
+    const uint32_t workers = (gridDim.x / g.n_xcd) * g.n_allowed_xcd;
+    uint32_t t = a != 0xFFu ? (blockIdx.x / g.n_xcd) * g.n_allowed_xcd + a : n_tiles;
+    prime(t);
     prologue();
     if (g.tlog && blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(&g.tlog[0], __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     uint32_t err = 0u;
-    if (a != 0xFFu) {
-        const uint32_t workers = (gridDim.x / g.n_xcd) * g.n_allowed_xcd;
-        for (uint32_t t = (blockIdx.x / g.n_xcd) * g.n_allowed_xcd + a; t < n_tiles; t += workers) {
-            log_tile(g, cu, t);
-            body(t, cu, err, NoOp());
-        }
-        if (a == 0u && blockIdx.x < g.n_xcd)
-            tail();
+    for (; t < n_tiles; t += workers) {
+        log_tile(g, cu, t);
+        body(t, t + workers, cu, err);
     }
+    if (a == 0u && blockIdx.x < g.n_xcd)
+        tail();
     if (g.tlog) {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -653,6 +656,24 @@ __device__ __forceinline__ void static_tile_loop(const Gate &g, uint32_t n_tiles
     }
     if (err != 0u)
         raise_flag(g.err, err);
+}
+
+struct NoPrime {
+    __device__ void operator()(uint32_t) const {}
+};
+
+// The same for bodies that take one tile at a time (``prologue`` and ``body``
+// as in gated_tile_loop; ``claim`` has no effect).
+template <typename Prologue, typename Body, typename Tail = NoOp>
+__device__ __forceinline__ void static_tile_loop(const Gate &g, uint32_t n_tiles, Prologue prologue,
+                                                 Body body, Tail tail = Tail())
+{
+    static_tile_stream(
+        g, n_tiles, NoPrime(), prologue,
+        [&](uint32_t t, uint32_t, uint32_t cu, uint32_t &err) __attribute__((always_inline)) {
+            body(t, cu, err, NoOp());
+        },
+        tail);
 }
 
 // The gate's two schedules behind one call: static for masks of whole XCDs

@@ -17,6 +17,8 @@
 // 16x16x32 MFMA: a 16-row block of W is the A operand, x (batch padded to 16
 // columns) the B operand; eight wavefronts split each chunk of K.  From batch
 // 3 on it measured faster than the vector path on MI355X.
+#include <algorithm>
+
 #include "host_common.hpp"
 
 namespace sgdrc {
@@ -273,6 +275,240 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_valu(
         raise_flag(g.err, pro_err);
 }
 
+// A row of W through its own buffer resource, for tiles that lie inside one
+// page (the common case: a 2 MiB page holds many tiles): base = the row's
+// first byte in the pool, range = the row's bytes, or 0 for a row past M or
+// a page-table entry outside the pool.  Loads then take the lane's offset in
+// the row and read zeros past it, with no table read, select or branch per
+// load.
+__device__ __forceinline__ Rsrc row_rsrc(uint64_t phys_row, bool valid, uint64_t row_bytes)
+{
+    return make_rsrc(reinterpret_cast<const void *>(phys_row), valid ? (uint32_t)row_bytes : 0u);
+}
+
+// The physical address of a tile's first byte when the tile lies inside
+// one page (the entry of that page; a bad entry is reported by the caller's
+// validity test), made wave-uniform so that resources built from it live in
+// scalar registers.
+__device__ __forceinline__ uint64_t tile_phys(const uint8_t *w_pool, uint32_t entry, uint64_t t_lo,
+                                              uint32_t shift, uint64_t pmask)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(w_pool) + ((uint64_t)entry << shift) + (t_lo & pmask);
+    // (the builtin returns int: each half goes through uint32_t, so that
+    // the low half is not sign-extended into the high one)
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return (uint64_t)lo | (uint64_t)hi << 32;
+}
+
+// ---- rows that one round of loads covers, under the static schedule
+//
+// The tile loop above issues a tile's loads, waits for them, sums, and only
+// then starts the next tile, so a wavefront has nothing in flight while it
+// reduces.  Here a wavefront's U loads form a ring: as soon as a slice of W is
+// summed, its register is reloaded with the same slice of the next row (of
+// the next tile after the tile's last row, which the static schedule knows),
+// so U loads per lane stay in flight throughout, and a tile costs one barrier
+// (s_red alternates).  The sums and their order are those of the kernel
+// above: the same bits.  Every row is read through a buffer resource of its
+// own; the few that cross into another page are summed from per-slice lookups
+// at their turn, which empties the ring, so pages hold at least
+// kRingRowsPerPage rows (64 KiB pages, 6000-byte rows: 47.8 against 42.8 us
+// for four calls).  The entries of W's whole table are staged in LDS (at most
+// kRingPages); the first tile's is read directly so that its loads start
+// before the staging ends.
+//
+// HBM-bound: bf16, batch 1, 2 MiB pages, 12 rotated copies, on MI355X, four
+// calls in a row, tile loop / ring: 4096 x 11008 on 256 CUs 68.3 / 64.7 us, on
+// 64 CUs 159.6 / 153.3; 11008 x 4096 67.3 / 63.8 and 164.2 / 150.9; 8192 x 5632
+// 72.6 / 64.6; batch 2, 11008 x 4096 on 64 CUs 172.0 / 156.5, on 256 CUs 69.5 /
+// 69.0.  (A plain read of 90 MB takes 14.1 us a launch.)  Three workgroups per
+// CU were up to 26 percent slower on 64 CUs, six or eight up to 8 percent.
+constexpr uint32_t kRingPages = 2048;
+constexpr int kRingWgsPerCu = 5;
+constexpr uint64_t kRingRowsPerPage = 32;
+
+template <int WT, int XT, int NB, int R, int U, bool XO>
+__global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
+    const uint8_t *__restrict__ w_pool, const uint32_t *__restrict__ pt, uint64_t pool_pages,
+    uint32_t M, uint32_t K, const uint8_t *__restrict__ x, uint32_t nb, float *__restrict__ y,
+    uint32_t shift, uint32_t n_tiles, Gate g)
+{
+    constexpr int WSZ = Dt<WT>::size, XSZ = Dt<XT>::size;
+    constexpr int EPV = 16 / WSZ;
+    constexpr int XW = EPV * XSZ / 4;
+    __shared__ uint32_t s_pt[kRingPages];
+    __shared__ float s_red[2][kGemvWaves][R * NB];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const uint32_t row_bytes = K * (uint32_t)WSZ;  // at most U * 4 KiB
+    const uint32_t KV = row_bytes / 16u;
+    const uint64_t pmask = (1ull << shift) - 1ull;
+    const uint32_t w_pages = (uint32_t)(((uint64_t)M * row_bytes + pmask) >> shift);
+    uint32_t pro_err = 0u;
+
+    // x of this lane's slices for every batch row (zeros out of range)
+    auto load_x = [&](uint32_t (&xs)[U][NB][XW]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t kv = (uint32_t)u * kGemvThreads + threadIdx.x;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                for (int i = 0; i < XW; ++i)
+                    xs[u][b][i] = 0u;
+                if (kv < KV && (uint32_t)b < nb) {
+                    const uint8_t *xp = x + ((uint64_t)b * K + (uint64_t)kv * EPV) * XSZ;
+                    if (XW == 2) {
+                        u32x2 v = *reinterpret_cast<const u32x2 *>(xp);
+                        xs[u][b][0] = v.x;
+                        xs[u][b][1] = v.y;
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < XW / 4; ++q) {
+                            u32x4 v = *reinterpret_cast<const u32x4 *>(xp + 16 * q);
+                            xs[u][b][4 * q + 0] = v.x;
+                            xs[u][b][4 * q + 1] = v.y;
+                            xs[u][b][4 * q + 2] = v.z;
+                            xs[u][b][4 * q + 3] = v.w;
+                        }
+                    }
+                }
+            }
+        }
+    };
+    // A row's bytes through a buffer resource of its own; the rare row that
+    // crosses into another page (``split``), like a row past M or on a page
+    // outside the pool, has an empty one and is read by split_row instead.
+    struct Row {
+        Rsrc r;
+        bool split;
+    };
+    auto row_of = [&](uint32_t m, bool staged) __attribute__((always_inline)) {
+        Row w;
+        const uint64_t at = (uint64_t)m * row_bytes;
+        const uint64_t p0 = at >> shift;
+        w.split = m < M && p0 != (at + row_bytes - 1u) >> shift;
+        const uint32_t j = m < M ? (uint32_t)p0 : 0u;
+        const uint32_t raw = staged ? s_pt[j] : pt[j];
+        const uint32_t e = __builtin_amdgcn_readfirstlane((uint64_t)raw < pool_pages ? raw : kBadPage);
+        w.r = row_rsrc(tile_phys(w_pool, e, at, shift, pmask), m < M && !w.split && e != kBadPage, row_bytes);
+        return w;
+    };
+    auto split_row = [&](uint32_t m, int u) __attribute__((always_inline)) {
+        const uint32_t kv = (uint32_t)u * kGemvThreads + threadIdx.x;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (kv < KV) {
+            const uint64_t off = (uint64_t)m * row_bytes + (uint64_t)kv * 16u;
+            const uint32_t p = s_pt[off >> shift];
+            if (p != kBadPage)
+                v = load_nt(w_pool + ((uint64_t)p << shift) + (off & pmask));
+        }
+        return v;
+    };
+    auto add_slice = [&](const u32x4 &w, uint32_t (&xs)[NB][XW], float (&acc)[NB]) __attribute__((always_inline)) {
+        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+        float wf[EPV];
+        decode<WT, EPV>(ww, wf);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            // (decoded here each time: kept decoded, x would take twice the
+            // registers and halve the wavefronts)
+#pragma unroll
+            for (int i = 0; i < XW; ++i)
+                asm volatile("" : "+v"(xs[b][i]));
+            float xf[EPV];
+            decode<XT, EPV>(xs[b], xf);
+#pragma unroll
+            for (int e = 0; e < EPV; ++e)
+                acc[b] = __builtin_fmaf(wf[e], xf[e], acc[b]);
+        }
+    };
+    const uint32_t off0 = threadIdx.x * 16u;
+
+    u32x4 wv[U];
+    uint32_t xk[U][NB][XW];
+    uint32_t ph = 0u;
+    bool split = false;  // the row whose loads are in the ring
+    auto prime = [&](uint32_t t) __attribute__((always_inline)) {
+        const Row w = row_of(t < n_tiles ? t * R : M, false);
+        split = w.split;
+        // x first: loads complete in order, so that the loop's first use of
+        // x does not wait for W
+        load_x(xk);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // in the order of use, which the loop's waits count on
+            __builtin_amdgcn_sched_barrier(0);
+            wv[u] = buf_load_nt(w.r, off0 + (uint32_t)u * kGemvThreads * 16u);
+        }
+    };
+    auto prologue = [&]() __attribute__((always_inline)) {
+        for (uint32_t i = threadIdx.x; i < w_pages; i += kGemvThreads)
+            s_pt[i] = checked_page(pt, i, pool_pages, pro_err);
+    };
+    auto body = [&](uint32_t t, uint32_t next, uint32_t, uint32_t &) __attribute__((always_inline)) {
+        const uint32_t m0 = t * R;
+        uint32_t xn[XO ? 1 : U][XO ? 1 : NB][XO ? 1 : XW];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const Row nxt = row_of(r + 1 < R ? m0 + r + 1u : next < n_tiles ? next * R : M, true);
+            // x of the next tile, before that tile's first loads of W
+            if constexpr (!XO) {
+                if (r + 1 == R)
+                    load_x(xn);
+            }
+            float acc[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                acc[b] = 0.0f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                add_slice(wv[u], xk[u], acc);
+                wv[u] = buf_load_nt(nxt.r, off0 + (uint32_t)u * kGemvThreads * 16u);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (split) {  // the ring held zeros for it
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    add_slice(split_row(m0 + r, u), xk[u], acc);
+            }
+            split = nxt.split;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                float v = acc[b];
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1)
+                    v += __shfl_xor(v, off, 64);
+                if (lane == 0)
+                    s_red[ph][wave][r * NB + b] = v;
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x < (uint32_t)(R * NB)) {
+            const uint32_t r = threadIdx.x / NB, b = threadIdx.x % NB;
+            float v = s_red[ph][0][threadIdx.x];
+#pragma unroll
+            for (int w = 1; w < kGemvWaves; ++w)
+                v += s_red[ph][w][threadIdx.x];
+            if (b < nb && m0 + r < M)
+                y[(uint64_t)b * M + m0 + r] = v;
+        }
+        ph ^= 1u;
+        if constexpr (!XO) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int i = 0; i < XW; ++i)
+                        xk[u][b][i] = xn[u][b][i];
+        }
+    };
+    static_tile_stream(g, n_tiles, prime, prologue, body, NoOp());
+    if (pro_err)
+        raise_flag(g.err, pro_err);
+}
+
 template <int DT>
 __device__ __forceinline__ f32x4 mfma16x16x32(u32x4 a, u32x4 b, f32x4 c)
 {
@@ -315,32 +551,6 @@ constexpr uint32_t kXOutside = 0xFFFFFFF0u;  // offset past any x resource
 __device__ __forceinline__ u32x4 buf_load(Rsrc r, uint32_t off)
 {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-
-// A row of W through its own buffer resource, for tiles that lie inside one
-// page (the common case: a 2 MiB page holds many tiles): base = the row's
-// first byte in the pool, range = the row's bytes, or 0 for a row past M or
-// a page-table entry outside the pool.  Loads then take the lane's offset in
-// the row and read zeros past it, with no table read, select or branch per
-// load.
-__device__ __forceinline__ Rsrc row_rsrc(uint64_t phys_row, bool valid, uint64_t row_bytes)
-{
-    return make_rsrc(reinterpret_cast<const void *>(phys_row), valid ? (uint32_t)row_bytes : 0u);
-}
-
-// The physical address of a tile's first byte when the tile lies inside
-// one page (the entry of that page; a bad entry is reported by the caller's
-// validity test), made wave-uniform so that resources built from it live in
-// scalar registers.
-__device__ __forceinline__ uint64_t tile_phys(const uint8_t *w_pool, uint32_t entry, uint64_t t_lo,
-                                              uint32_t shift, uint64_t pmask)
-{
-    const uint64_t a = reinterpret_cast<uint64_t>(w_pool) + ((uint64_t)entry << shift) + (t_lo & pmask);
-    // (the builtin returns int: each half goes through uint32_t, so that
-    // the low half is not sign-extended into the high one)
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    return (uint64_t)lo | (uint64_t)hi << 32;
 }
 
 // XA: x is staged for the whole K in LDS once per workgroup (rows of at
@@ -687,6 +897,35 @@ static GemvKernel valu_kernel(const sgdrc_gemv_plan &p)
     return nullptr;
 }
 
+// The ring kernel of a vector plan whose rows one round of loads covers, for
+// W and x of one type and a table that its LDS holds; launched under the
+// static schedule only (the queues name a tile too late to load ahead).  Its
+// ring has as many loads as a row needs (the plan's ``loads`` at most).
+static GemvKernel ring_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype, uint64_t row_bytes,
+                              uint64_t w_pages, uint64_t page_bytes)
+{
+    const uint64_t slots = (row_bytes + kGemvThreads * 16u - 1u) / (kGemvThreads * 16u);
+    if (p.path != SGDRC_GEMV_VALU || w_dtype != x_dtype || w_pages > kRingPages || slots > p.loads ||
+        row_bytes * kRingRowsPerPage > page_bytes)
+        return nullptr;
+#define SGDRC_RING(NB, R, U, XO)                                                       \
+    if (p.batch_cols == NB && p.rows == R && slots == U && p.x_once == (XO ? 1u : 0u)) { \
+        if (w_dtype == SGDRC_BF16)                                                     \
+            return k_gemv_ring<SGDRC_BF16, SGDRC_BF16, NB, R, U, XO>;                  \
+        return w_dtype == SGDRC_F16 ? k_gemv_ring<SGDRC_F16, SGDRC_F16, NB, R, U, XO>  \
+                                    : k_gemv_ring<SGDRC_F32, SGDRC_F32, NB, R, U, XO>; \
+    }
+    SGDRC_RING(1, 2, 6, true)
+    SGDRC_RING(1, 2, 5, true)
+    SGDRC_RING(1, 2, 4, true)
+    SGDRC_RING(1, 2, 3, true)
+    SGDRC_RING(1, 4, 2, false)
+    SGDRC_RING(2, 4, 3, true)
+    SGDRC_RING(2, 4, 2, true)
+#undef SGDRC_RING
+    return nullptr;
+}
+
 template <int WT>
 static GemvKernel valu_kernel_x(int x_dtype, const sgdrc_gemv_plan &p)
 {
@@ -807,16 +1046,22 @@ int colored_gemv(sgdrc_ctx *ctx, const sgdrc_paged *w, int w_dtype, uint32_t M, 
     const sgdrc_gemv_plan plan =
         make_plan((uint32_t)std::max(1, stream_allowed_cus(c, stream)), w_dtype, M, K, x_dtype,
                   batch);
-    const GemvKernel k = plan_kernel(plan, w_dtype, x_dtype);
-    if (!k)
-        return set_error(SGDRC_EINVAL, "no kernel for the plan (library fault)");
     Gate g;
     LaunchInfo li;
     rc = make_gate(c, stream, plan.tiles, kGemvGroupCus, &g, &li, false, true);
     if (rc)
         return rc;
+    const uint64_t row_bytes = (uint64_t)K * dtype_size(w_dtype);
+    const uint64_t w_pages = ((uint64_t)M * row_bytes + (1ull << page_shift) - 1u) >> page_shift;
+    GemvKernel k = g.statics ? ring_kernel(plan, w_dtype, x_dtype, row_bytes, w_pages, 1ull << page_shift) : nullptr;
+    const bool ring = k != nullptr;
+    if (!ring)
+        k = plan_kernel(plan, w_dtype, x_dtype);
+    if (!k)
+        return set_error(SGDRC_EINVAL, "no kernel for the plan (library fault)");
     const int threads = plan.path == SGDRC_GEMV_MFMA ? kMfmaThreads : kGemvThreads;
-    const uint32_t grid = gated_grid(c, kernel_occupancy(k, threads), plan.tiles, li);
+    const int occ = kernel_occupancy(k, threads);
+    const uint32_t grid = gated_grid(c, ring ? std::min(occ, kRingWgsPerCu) : occ, plan.tiles, li);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k, dim3(grid), dim3(threads), 0, s, static_cast<const uint8_t *>(w->pool),
                        w->pt, w->pool_pages, M, K, static_cast<const uint8_t *>(d_x), batch, d_y,
