@@ -76,6 +76,7 @@ int stream_state(Ctx *c, void *stream, StreamState **out)
         StreamState st;
         st.slot = slot;
         st.mask = c->all_cus;
+        st.mi = c->all_info;
         it = c->streams.emplace(stream, st).first;
     }
     *out = &it->second;
@@ -96,32 +97,45 @@ static uint32_t xcc_allowed(const Ctx *c, const sgdrc_cu_mask &m)
     return bits;
 }
 
-// The rank of each XCC_ID among the XCDs that ``m`` allows (0xFF: not
-// allowed) and their number, or 0 when an XCD is allowed in part.
-static uint32_t whole_xcds(const Ctx *c, const sgdrc_cu_mask &m, uint8_t rank[kMaxXcds])
+static int mask_info(const Ctx *c, const sgdrc_cu_mask &m, MaskInfo *mi)
 {
-    std::memset(rank, 0xFF, kMaxXcds);
-    uint32_t a = 0;
+    *mi = MaskInfo{};
+    std::memset(mi->rank, 0xFF, sizeof mi->rank);
+    uint32_t groups = 0, ranks = 0;
+    bool whole = true;
     for (int x = 0; x < c->n_xcds; ++x) {
-        int on = 0;
         const int first = c->xcd_first_cu[x], count = c->xcd_first_cu[x + 1] - first;
-        for (int cu = first; cu < first + count; ++cu)
+        const uint32_t subs = (uint32_t)(count + (1 << kGroupShift) - 1) >> kGroupShift;
+        if (groups + subs > (uint32_t)kMaxGroups)
+            return set_error(SGDRC_EINVAL, "too many queue groups");
+        mi->grp_base[x] = (uint8_t)groups;
+        int on = 0;
+        for (int i = 0; i < count; ++i) {
+            if (i % (1 << kGroupShift) == 0)
+                mi->before[groups + (uint32_t)(i >> kGroupShift)] = (uint16_t)(mi->allowed + on);
+            const int cu = first + i;
             on += (int)((m.bits[cu >> 6] >> (cu & 63)) & 1ull);
+        }
+        groups += subs;
+        mi->allowed += on;
         if (on == count)
-            rank[(c->keys[first] >> 8) & 0xFu] = (uint8_t)a++;
-        else if (on != 0)
-            return 0;
+            mi->rank[(c->keys[first] >> 8) & 0xFu] = (uint8_t)ranks++;
+        whole = whole && (on == 0 || on == count);
     }
-    return a;
+    for (uint32_t g = groups; g <= (uint32_t)kMaxGroups; ++g)
+        mi->before[g] = (uint16_t)mi->allowed;
+    mi->n_groups = groups;
+    mi->xcc_allowed = xcc_allowed(c, m);
+    mi->whole_xcds = whole && c->static_ok ? ranks : 0u;
+    return SGDRC_OK;
 }
 
 int static_cus(Ctx *c, void *stream)
 {
     std::lock_guard<std::mutex> lock(c->mu);
     auto it = c->streams.find(stream);
-    const sgdrc_cu_mask &m = it != c->streams.end() ? it->second.mask : c->all_cus;
-    uint8_t rank[kMaxXcds];
-    return c->static_ok && whole_xcds(c, m, rank) ? popcount_mask(m) : 0;
+    const MaskInfo &mi = it != c->streams.end() ? it->second.mi : c->all_info;
+    return mi.whole_xcds ? mi.allowed : 0;
 }
 
 int make_gate(Ctx *c, void *stream, uint64_t n_tiles, int group_cus, Gate *g, LaunchInfo *li,
@@ -153,64 +167,38 @@ int make_gate(Ctx *c, void *stream, uint64_t n_tiles, int group_cus, Gate *g, La
         g->tlog = st->tlog + 2u * (st->tlog_next % st->tlog_slots);
         ++st->tlog_next;
     }
-    // queue groups: runs of group_cus CUs inside each XCD, or one group
-    uint32_t shift = 0;
-    while ((1 << (shift + 1)) <= group_cus && shift < 5)
-        ++shift;
-    const bool single = group_cus <= 0;
-    if (single)
-        shift = 8;  // every CU-in-XCD index (< 256) maps to sub-group 0
-    uint64_t allowed[kMaxGroups] = {};
-    uint64_t total = 0;
-    int n_groups = 0;
-    std::memset(g->grp_base, 0, sizeof g->grp_base);
-    for (int x = 0; x < c->n_xcds; ++x) {
-        const int first = c->xcd_first_cu[x], count = c->xcd_first_cu[x + 1] - first;
-        const int subs = single ? 0 : (count + (1 << shift) - 1) >> shift;
-        if (n_groups + subs > kMaxGroups)
-            return set_error(SGDRC_EINVAL, "too many queue groups");
-        g->grp_base[x] = (uint8_t)n_groups;
-        for (int i = 0; i < count; ++i) {
-            const int cu = first + i;
-            const uint64_t bit = (st->mask.bits[cu >> 6] >> (cu & 63)) & 1ull;
-            allowed[single ? 0 : n_groups + (i >> shift)] += bit;
-            total += bit;
-        }
-        n_groups += subs;
-    }
-    if (single) {
-        n_groups = 1;
-        std::memset(g->grp_base, 0, sizeof g->grp_base);
-    }
-    uint64_t cum = 0;
-    g->grp_tile[0] = 0;
-    for (int grp = 0; grp < kMaxGroups; ++grp) {
-        cum += allowed[grp];
-        g->grp_tile[grp + 1] = (uint32_t)(total ? n_tiles * cum / total : n_tiles);
-    }
+    const MaskInfo &mi = st->mi;
+    const uint64_t total = (uint64_t)mi.allowed;
     if (total == 0)
         return set_error(SGDRC_EINVAL, "the stream's CU mask allows no CU of this device");
-    g->n_groups = (uint32_t)n_groups;
-    g->grp_shift = shift;
-    g->xcc_allowed = xcc_allowed(c, st->mask);
     // static schedule: every XCD either wholly allowed or wholly not
-    g->statics = 0u;
-    std::memset(g->xcd_rank, 0xFF, sizeof g->xcd_rank);
-    g->n_allowed_xcd = 0u;
+    g->statics = allow_static && !preemptible && mi.whole_xcds ? 1u : 0u;
+    std::memcpy(g->xcd_rank, mi.rank, sizeof g->xcd_rank);
+    g->n_allowed_xcd = mi.whole_xcds;
     g->n_xcd = (uint32_t)c->n_xcds;
-    if (allow_static && !preemptible && c->static_ok) {
-        uint8_t rank[kMaxXcds];
-        const uint32_t a = whole_xcds(c, st->mask, rank);
-        if (a > 0) {
-            g->statics = 1u;
-            std::memcpy(g->xcd_rank, rank, sizeof rank);
-            g->n_allowed_xcd = a;
-        }
+    g->xcc_allowed = mi.xcc_allowed;
+    // queue groups: runs of 8 CUs inside each XCD, or one group (with a
+    // static schedule no kernel reads them)
+    if (group_cus > 0) {
+        g->grp_shift = (uint32_t)kGroupShift;
+        g->n_groups = mi.n_groups;
+        std::memcpy(g->grp_base, mi.grp_base, sizeof g->grp_base);
+        if (!g->statics)
+            for (int grp = 0; grp <= kMaxGroups; ++grp)
+                g->grp_tile[grp] = (uint32_t)(n_tiles * mi.before[grp] / total);
+    } else {
+        g->grp_shift = 8;  // every CU-in-XCD index (< 256) maps to group 0
+        g->n_groups = 1;
+        std::memset(g->grp_base, 0, sizeof g->grp_base);
+        g->grp_tile[0] = 0;
+        for (int grp = 1; grp <= kMaxGroups; ++grp)
+            g->grp_tile[grp] = (uint32_t)n_tiles;
     }
     st->last_schedule = g->statics;
     st->last_tiles = n_tiles;
-    li->allowed = (int)total;
+    li->allowed = mi.allowed;
     li->wg_cap = st->wg_cap;
+    li->static_xcds = g->statics ? mi.whole_xcds : 0u;
     return SGDRC_OK;
 }
 
@@ -292,7 +280,7 @@ int stream_allowed_cus(Ctx *c, void *stream)
 {
     std::lock_guard<std::mutex> lock(c->mu);
     auto it = c->streams.find(stream);
-    return popcount_mask(it != c->streams.end() ? it->second.mask : c->all_cus);
+    return (it != c->streams.end() ? it->second.mi : c->all_info).allowed;
 }
 
 bool stream_preemptible(Ctx *c, void *stream)
@@ -321,7 +309,12 @@ uint32_t gated_grid(const Ctx *c, int blocks_per_cu, uint64_t n_tiles, const Lau
     const uint64_t allowed = (uint64_t)std::max(li.allowed, 1);
     const uint64_t per_cu_tiles = (n_tiles + allowed - 1) / allowed;
     const uint64_t per_cu = std::max<uint64_t>(1, std::min<uint64_t>(fit, per_cu_tiles));
-    return (uint32_t)(per_cu * (uint64_t)c->num_cus);
+    uint64_t grid = per_cu * (uint64_t)c->num_cus;
+    if (li.static_xcds) {
+        const uint64_t need = std::max<uint64_t>(1, (n_tiles + li.static_xcds - 1) / li.static_xcds);
+        grid = std::min<uint64_t>(grid, need * (uint64_t)c->n_xcds);
+    }
+    return (uint32_t)grid;
 }
 
 int check_hash(const sgdrc_hash *h)
@@ -446,6 +439,9 @@ static int probe_topology(Ctx *c, int expected)
     std::memset(&c->all_cus, 0, sizeof c->all_cus);
     for (int i = 0; i < expected; ++i)
         c->all_cus.bits[i >> 6] |= 1ull << (i & 63);
+    const int rc = mask_info(c, c->all_cus, &c->all_info);
+    if (rc)
+        return rc;
     SGDRC_HIP(hipMemcpy(c->d_lut, lut.data(), kLutSize * sizeof(uint32_t), hipMemcpyHostToDevice));
     return SGDRC_OK;
 }
@@ -703,8 +699,12 @@ int set_cu_mask(sgdrc_ctx *ctx, void *stream, const sgdrc_cu_mask *mask)
     rc = stream_state(c, stream, &st);
     if (rc)
         return rc;
+    MaskInfo mi = c->all_info;
+    if (mask && (rc = mask_info(c, *mask, &mi)))
+        return rc;
     std::lock_guard<std::mutex> lock(c->mu);
     st->mask = mask ? *mask : c->all_cus;
+    st->mi = mi;
     return SGDRC_OK;
 }
 

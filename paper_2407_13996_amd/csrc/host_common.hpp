@@ -30,14 +30,31 @@ constexpr int kHistAccCopies = 8;
 // over per-XCD queues.  Short kernels such as the GEMV use queues of a few
 // CUs, so that fewer workgroups contend on each counter.
 constexpr int kStreamGroupCus = 0;
-constexpr int kGemvGroupCus = 8;
+constexpr int kGroupShift = 3;
+constexpr int kGemvGroupCus = 1 << kGroupShift;
 
 // Re-issues a preemptible launch with a given gate and grid size.
 typedef std::function<hipError_t(const Gate &, uint32_t grid)> Relaunch;
 
+// What launches need of a CU mask, worked out once when the mask is set.
+struct MaskInfo {
+    int allowed = 0;                  // allowed CUs
+    uint32_t xcc_allowed = 0;         // physical XCC ids with allowed CUs
+    // masks of whole XCDs: how many are allowed (0: some XCD is allowed in
+    // part) and the rank of each XCC id among them (0xFF: not allowed)
+    uint32_t whole_xcds = 0;
+    uint8_t rank[kMaxXcds];
+    // queue groups of 8 CUs: their number, the first of each XCD, and the
+    // allowed CUs in the groups before each
+    uint32_t n_groups = 0;
+    uint8_t grp_base[kMaxXcds];
+    uint16_t before[kMaxGroups + 1];
+};
+
 struct StreamState {
     int slot = -1;
     sgdrc_cu_mask mask{};
+    MaskInfo mi{};
     uint32_t wg_cap = 0;        // workgroups per CU at most (0 = as many as fit)
     uint64_t last_tiles = 0;
     uint64_t *tlog = nullptr;   // time-log slots ({start, end} pairs) or NULL
@@ -61,6 +78,7 @@ struct StreamState {
 struct LaunchInfo {
     int allowed = 0;            // allowed CUs
     uint32_t wg_cap = 0;        // per-stream cap on workgroups per CU
+    uint32_t static_xcds = 0;   // allowed XCDs of a statically scheduled launch, else 0
 };
 
 struct Ctx {
@@ -70,6 +88,7 @@ struct Ctx {
     uint32_t wallclock_khz = 0;          // rate of the counter read by s_memrealtime
     uint32_t keys[SGDRC_MAX_CUS] = {};   // logical CU -> hardware key
     sgdrc_cu_mask all_cus{};
+    MaskInfo all_info{};
     int n_xcds = 0;
     int xcd_first_cu[kMaxXcds + 1] = {};  // logical CUs of XCD x: [first[x], first[x+1])
     // the dispatcher hands workgroup i of a grid to the XCD of workgroup
@@ -128,8 +147,8 @@ int check_ctx(const sgdrc_ctx *ctx, Ctx **out);
 int stream_state(Ctx *c, void *stream, StreamState **out);
 
 // Gate arguments for a launch of ``n_tiles`` tiles on ``stream`` whose work
-// queues serve runs of ``group_cus`` CUs inside an XCD (a power of two, at
-// most 32), or the whole device (0).  ``preemptible``: the launch uses the
+// queues serve runs of ``group_cus`` = 8 CUs inside an XCD, or the whole device
+// (0).  ``preemptible``: the launch uses the
 // stream's preemptible queue slot and eviction flag (the stream must have
 // eviction on).
 int make_gate(Ctx *c, void *stream, uint64_t n_tiles, int group_cus, Gate *g, LaunchInfo *li,
@@ -163,7 +182,10 @@ void record_preemptible(Ctx *c, void *stream, const Gate &g, uint64_t n_tiles, i
 // Grid size for a gated persistent kernel: the same number of workgroups
 // for every CU (the dispatcher spreads them over all CUs; those on CUs
 // outside the mask leave at once), as many as fit at once (or the stream's
-// cap) but no more than the tiles that fall to one allowed CU.
+// cap) but no more than the tiles that fall to one allowed CU; under the
+// static schedule no more than a workgroup per tile on each allowed XCD (at
+// least one per XCD), which the queues cannot promise (their workgroups may
+// land on CUs outside the mask).
 uint32_t gated_grid(const Ctx *c, int blocks_per_cu, uint64_t n_tiles, const LaunchInfo &li);
 
 int popcount_mask(const sgdrc_cu_mask &m);
