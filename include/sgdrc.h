@@ -44,9 +44,8 @@
  *    n mod 16 bytes of a relayout or triad, the last n mod 16 addresses of
  *    a classify) and, on the ticket queues, any tiles left if no workgroup
  *    reached an allowed CU are handled by the grid's last workgroup, which
- *    may sit on any CU; under the static schedule (see set_cu_mask) a
- *    classify's remainder and histogram total are produced by a
- *    one-workgroup kernel enqueued right after the grid, also on any CU.
+ *    may sit on any CU; under the static schedule (see set_cu_mask) the
+ *    remainder of a relayout or triad is moved on an allowed CU.
  */
 #ifndef SGDRC_H
 #define SGDRC_H
@@ -148,10 +147,10 @@ int sgdrc_last_tiles(sgdrc_ctx *ctx, void *stream, uint64_t *tiles);
 
 /* How the last launch enqueued on ``stream`` distributed its tiles:
  * SGDRC_SCHED_QUEUE (atomic ticket queues per group of CUs, with stealing)
- * or SGDRC_SCHED_STATIC (colored_gemv, colour_classify and
- * colour_classify_table under a mask made of whole XCDs: each workgroup
- * derives its tiles from its XCD and index, no atomics).  For tests and
- * tools. */
+ * or SGDRC_SCHED_STATIC (colored_gemv, colour_classify, colour_classify_table
+ * and short colored_stream and bimodal_relayout launches under a mask made of
+ * whole XCDs: each workgroup derives its tiles from its XCD and index, no
+ * tickets).  For tests and tools. */
 enum { SGDRC_SCHED_QUEUE = 0, SGDRC_SCHED_STATIC = 1 };
 int sgdrc_last_schedule(sgdrc_ctx *ctx, void *stream, uint32_t *schedule);
 
@@ -188,8 +187,9 @@ int sgdrc_set_stream_occupancy(sgdrc_ctx *ctx, void *stream, uint32_t max_wgs_pe
  * set used by every later launch on ``stream``: each workgroup reads its
  * CU identity from the hardware registers and exits unless that CU is in
  * the set; the remaining workgroups take tiles from an atomic queue until it
- * is empty.  A colored_gemv or colour_classify under a mask made of whole
- * XCDs (the usual case: all CUs, or n x 32 CUs) needs no queue: the
+ * is empty.  A colored_gemv, a colour_classify or a short colored_stream or
+ * bimodal_relayout under a mask made of whole XCDs (the usual case: all CUs,
+ * or n x 32 CUs) needs no queue: the
  * hardware hands
  * workgroup i of a grid to the XCD of workgroup i mod (XCD count), which
  * sgdrc_init checks, so a workgroup on an allowed XCD derives its tiles from

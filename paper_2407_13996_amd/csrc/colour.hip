@@ -116,16 +116,13 @@ constexpr uint32_t kPhasedGroup = 16;  // gathers in flight per lane
 constexpr uint32_t kSliceShift = 21;
 constexpr int kPhasedWgsPerCu = 4;
 
-// Histogram bins are replicated once per lane in LDS (copy = lane), so that
-// no two lanes of a wavefront ever add to one address (bin-major, so a
-// wavefront's 64 adds to one bin fall in 64 consecutive dwords).  On
-// MI355X, 2^26 addresses with K = 6: 97.1 us of kernel span against 99.2
-// with 8, 16 or 32 copies.  16 KiB of LDS per workgroup at K = 6, 64 KiB
-// for 256 bins (two workgroups per CU still fit).  The table kernels take 16
-// copies: they are bound by their gathers, and the shorter flush is worth
-// more (2^24 addresses in a 64 KiB table: 59 against 65 us).
-constexpr int kHistCopies = 64;
-constexpr int kHistTableCopies = 16;
+// Histogram bins are replicated 16 times in LDS (copy = lane mod 16,
+// bin-major), so that lanes of a wavefront seldom add to one address.  More
+// copies cost more to clear and to sum than they save: 16 / 64 copies (one per
+// lane) on MI355X, 65536 addresses, K = 4 6.6 / 7.2 us, K = 6 7.0 / 8.0, K = 8
+// 7.7 / 12.5; 2^26 addresses, K = 4 102.4 / 103.7 us, K = 6 102.9 / 102.4, K = 8
+// 101.5 / 112.1, a 64 KiB colour table (2^24 addresses) 59 / 65.
+constexpr int kHistCopies = 16;
 
 // hist_out[b] = the sum of bin b over the kHistAccCopies accumulator copies,
 // which are cleared for the next launch (every thread of one workgroup).
@@ -188,7 +185,7 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
     constexpr bool TAB = FROM != ClsFrom::Hash;
     constexpr uint32_t kBins = 1u << K;
     constexpr uint32_t kTile = cls_wave_tile(LOADS);
-    constexpr int kCopies = TAB ? kHistTableCopies : kHistCopies;
+    constexpr int kCopies = kHistCopies;
     __shared__ uint32_t s_hist[HIST ? kBins * kCopies : 1];
     // per wavefront: the colour bytes of one tile, 2 per lane and load
     __shared__ __attribute__((aligned(16))) uint16_t s_col[kClsThreads / 64][kTile / 2];
@@ -309,7 +306,7 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
         }
     };
     if (g.statics)
-        static_wave_loop(g, n_tiles, prologue, body, flush);
+        static_wave_loop(g, n_tiles, prologue, body, flush, epilogue);
     else
         gated_wave_loop(g, n_tiles, prologue, body, flush, epilogue);
 }
@@ -336,31 +333,6 @@ __global__ __launch_bounds__(kClsThreads) void k_classify_slices(const uint64_t 
 {
     classify<8, HIST, ClsFrom::Slices, kPhasedLoads>(addrs, n, colours, h, tab, hist_acc, hist_out,
                                                      n_tiles, g);
-}
-
-// After a statically scheduled classify (one workgroup, stream-ordered
-// after it): colour the last n mod 16 addresses and publish the histogram
-// the workgroups accumulated in hist_acc, clearing it for the next launch.
-template <int K, bool HIST, bool TAB>
-__global__ __launch_bounds__(kClsThreads) void k_classify_finish(const uint64_t *__restrict__ addrs,
-                                                                 uint64_t n, uint8_t *__restrict__ colours,
-                                                                 HashArgs h, TableArgs tab,
-                                                                 uint64_t *hist_acc, uint64_t *hist_out)
-{
-    constexpr uint32_t kBins = 1u << K;
-    const uint64_t i = (n & ~15ull) + threadIdx.x;
-    if (i < n) {
-        const uint64_t a = addrs[i];
-        const uint32_t c = TAB ? table_colour(tab, a) : colour_of<K>((uint32_t)a, (uint32_t)(a >> 32), h);
-        colours[i] = (uint8_t)c;
-        if (HIST)
-            __hip_atomic_fetch_add(&hist_acc[c], (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (HIST) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        publish_histogram<kBins>(hist_acc, hist_out);
-    }
 }
 
 // ------------------------------------------------- page-table build
@@ -747,20 +719,14 @@ static int launch_classify(Ctx *c, const HashArgs &h, const TableArgs &tab,
                                    occupancy(k_classify<K, true, false>, kClsThreads)};
         per_cu = std::min(occ[d_hist != nullptr], per_cu);
     }
-    hipLaunchKernelGGL(k, dim3(gated_grid(c, per_cu, wg_tiles, li)), dim3(kClsThreads), 0, s,
-                       d_addrs, n, d_colours, h, tab, acc, d_hist, (uint32_t)n_tiles, g);
+    const uint32_t grid = gated_grid(c, per_cu, wg_tiles, li);
+    // the last n mod 16 addresses and the histogram's publication fall to the
+    // last workgroup (for 65536 addresses the call takes 7.2 us against 9.5
+    // with a kernel that follows the grid, for 2^26 the same)
+    g.arrive = g.statics && (d_hist || (n & 15u)) ? 1u : 0u;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kClsThreads), 0, s, d_addrs, n, d_colours, h, tab, acc,
+                       d_hist, (uint32_t)n_tiles, g);
     SGDRC_HIP(hipGetLastError());
-    if (g.statics) {
-        // the statically scheduled grid has no last workgroup: the tail and
-        // the histogram's publication follow in a kernel of their own
-        if (d_hist)
-            hipLaunchKernelGGL((k_classify_finish<K, true, TAB>), dim3(1), dim3(kClsThreads), 0, s,
-                               d_addrs, n, d_colours, h, tab, acc, d_hist);
-        else if (n & 15u)
-            hipLaunchKernelGGL((k_classify_finish<K, false, TAB>), dim3(1), dim3(kClsThreads), 0, s,
-                               d_addrs, n, d_colours, h, tab, acc, d_hist);
-        SGDRC_HIP(hipGetLastError());
-    }
     return finish_static_tlog(g, s);
 }
 

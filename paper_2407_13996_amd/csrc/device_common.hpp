@@ -105,6 +105,7 @@ struct Gate {
     uint8_t xcd_rank[kMaxXcds];
     uint32_t n_allowed_xcd;
     uint32_t n_xcd;
+    uint32_t arrive;             // static_wave_loop: 1 = the last workgroup runs the epilogue
 };
 
 // The testing aid of preemptible launches: whether tile ``tile`` is to be
@@ -836,12 +837,14 @@ __device__ __forceinline__ void gated_wave_loop(const Gate &g, uint32_t n_tiles,
 // as static_tile_loop): the workers are the wavefronts, numbered so that the
 // waves of one workgroup take consecutive tiles, and wave v of the W
 // workers takes tiles v, v + W, ...  ``flush`` runs once the workgroup's
-// waves are done; there is no last workgroup, so no epilogue: the host
+// waves are done.  With g.arrive the workgroups count their arrivals and the
+// last one runs ``epilogue``; without, there is no last workgroup and the host
 // enqueues whatever must follow the whole grid as a kernel of its own.
-template <typename Prologue, typename Body, typename Flush>
+template <typename Prologue, typename Body, typename Flush, typename Epilogue>
 __device__ __forceinline__ void static_wave_loop(const Gate &g, uint32_t n_tiles, Prologue prologue,
-                                                 Body body, Flush flush)
+                                                 Body body, Flush flush, Epilogue epilogue)
 {
+    __shared__ uint32_t s_flag;
     uint32_t xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
     const uint32_t a = g.xcd_rank[xcc & 0xFu];
@@ -862,6 +865,10 @@ __device__ __forceinline__ void static_wave_loop(const Gate &g, uint32_t n_tiles
             body(t, cu, err, NoOp());
         }
         flush();
+    }
+    if (g.arrive && arrive_last(g, &s_flag)) {
+        epilogue();
+        reset_slot(g.q);
     }
     if (g.tlog) {
         __builtin_amdgcn_s_waitcnt(0);
