@@ -778,6 +778,188 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         raise_flag(g.err, pro_err);
 }
 
+// The same GEMM under the static schedule for a W whose rows do not cross
+// pages and whose table fits in LDS: the chunk loads run on over tile ends.  The kernel above ends a tile with pad
+// chunks (nothing in flight) and fills its two register sets again for the
+// next; here the last two chunks of a tile load the first two of the
+// workgroup's next tile, and the sum over the waves overlaps them.  Same
+// chunks in the same order per output: the same bits.  Rows are read through
+// a buffer resource each, also where a tile spans pages.
+//
+// HBM-bound with the x staging beside it: bf16, 11008 x 4096 in 2 MiB pages, four
+// calls with 12 rotated copies on MI355X, by tiles / streaming: batch 8 on 256
+// CUs 76.9 / 71.6 us, 192 96.1 / 89.1, 128 139.5 / 126.7, 64 212.3 / 184.5; batch
+// 4 on 128 CUs 122.8 / 119.2, 64 175.4 / 164.6.
+template <int DT, int ROWS, int XB, bool XA>
+__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm_stream(
+    const uint8_t *__restrict__ w_pool, const uint32_t *__restrict__ pt, uint64_t pool_pages,
+    uint32_t M, uint32_t K, const uint8_t *__restrict__ x, uint32_t nb, float *__restrict__ y,
+    uint32_t shift, uint32_t n_tiles, Gate g)
+{
+    __shared__ uint32_t s_pt[kPtCap];
+    __shared__ f32x4 s_red[kMfmaWaves][64];
+    constexpr int WL = ROWS * (int)kMfmaChunkSlices / kMfmaThreads;  // W loads per lane
+    constexpr int XL = XB * (int)kMfmaChunkSlices / kMfmaThreads;    // x loads per lane
+    constexpr uint32_t kRowStep = kMfmaThreads / kMfmaChunkSlices;
+    static_assert(kMfmaSets == 2, "the last two chunks load the next tile's first two");
+    __shared__ __attribute__((aligned(16))) uint8_t s_w[ROWS][kMfmaLdsRow];
+    __shared__ __attribute__((aligned(16))) uint8_t s_x[XA ? 1 : XB][XA ? 16 : kMfmaLdsRow];
+    __shared__ __attribute__((aligned(16))) uint8_t s_xa[XA ? XB : 1][XA ? kXaBytes + 16u : 16u];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t rl = lane & 15u, grp = lane >> 4;
+    const uint32_t row_bytes = K * 2u;
+    const uint32_t KV = row_bytes / 16u;
+    const uint32_t n_chunks = (KV + kMfmaChunkSlices - 1u) / kMfmaChunkSlices;
+    const uint64_t pmask = (1ull << shift) - 1ull;
+    const uint64_t w_pages = ((uint64_t)M * row_bytes + pmask) >> shift;  // at most kPtCap
+    const Rsrc x_rsrc = make_rsrc(x, nb * row_bytes);
+    uint32_t pro_err = 0u;
+    const uint32_t w_sl = threadIdx.x % kMfmaChunkSlices;
+    const uint32_t w_r = __builtin_amdgcn_readfirstlane(threadIdx.x / kMfmaChunkSlices);
+    u32x4 ws[kMfmaSets][WL], xs[kMfmaSets][XL];
+
+    // a tile's rows (of one past the end: nothing to read)
+    struct Tile {
+        uint64_t at[WL];  // the rows' first bytes in the pool
+        bool on[WL];      // whether there is anything to read
+        uint32_t rot;
+    };
+    auto tile_of = [&](uint32_t t, bool staged) __attribute__((always_inline)) {
+        Tile d;
+        const uint32_t m0 = t < n_tiles ? t * (uint32_t)ROWS : M;
+        d.rot = (m0 / 16u) % n_chunks;
+#pragma unroll
+        for (int q = 0; q < WL; ++q) {
+            const uint32_t m = m0 + w_r + (uint32_t)q * kRowStep;
+            const uint64_t at = (uint64_t)(m < M ? m : 0u) * row_bytes;
+            const uint32_t raw = staged ? s_pt[at >> shift] : pt[at >> shift];
+            const uint32_t e = __builtin_amdgcn_readfirstlane((uint64_t)raw < pool_pages ? raw : kBadPage);
+            d.at[q] = tile_phys(w_pool, e, at, shift, pmask);
+            d.on[q] = m < M && e != kBadPage;
+        }
+        return d;
+    };
+    // chunk number ``cl`` of a tile's order; n_chunks for a pad
+    auto chunk_at = [&](uint32_t cl, uint32_t rot) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_readfirstlane(
+            cl >= n_chunks ? n_chunks : (cl + rot >= n_chunks ? cl + rot - n_chunks : cl + rot));
+    };
+    auto load_x = [&](uint32_t c, u32x4 *xv) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < (XA ? 0 : XL); ++q) {
+            const uint32_t L = (uint32_t)q * kMfmaThreads + threadIdx.x;
+            const uint32_t b = L / kMfmaChunkSlices, kv = c * kMfmaChunkSlices + L % kMfmaChunkSlices;
+            xv[q] = buf_load(x_rsrc, b < nb && kv < KV ? b * row_bytes + kv * 16u : kXOutside);
+        }
+    };
+    auto load_rows = [&](const Tile &d, uint32_t c, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < WL; ++q)
+            ws[s][q] = buf_load_nt(row_rsrc(d.at[q], d.on[q], row_bytes), c * kMfmaChunk + w_sl * 16u);
+        load_x(c, xs[s]);
+    };
+    Tile cur;
+    auto prime = [&](uint32_t t) __attribute__((always_inline)) {
+        cur = tile_of(t, false);
+#pragma unroll
+        for (int s = 0; s < kMfmaSets; ++s)
+            load_rows(cur, chunk_at((uint32_t)s, cur.rot), s);
+    };
+    auto prologue = [&]() __attribute__((always_inline)) {
+        stage_whole_table(pt, pool_pages, w_pages, s_pt, pro_err);
+        if (XA) {
+            constexpr uint32_t kSl = kXaBytes / 16u;
+#pragma unroll
+            for (int q = 0; q < XB * (int)kSl / kMfmaThreads; ++q) {
+                const uint32_t i = (uint32_t)q * kMfmaThreads + threadIdx.x;
+                const uint32_t b = i / kSl, sl = i % kSl;
+                *reinterpret_cast<u32x4 *>(&s_xa[b][sl * 16u]) =
+                    buf_load(x_rsrc, b < nb && sl < KV ? b * row_bytes + sl * 16u : kXOutside);
+            }
+        }
+    };
+    auto body = [&](uint32_t t, uint32_t next, uint32_t, uint32_t &) __attribute__((always_inline)) {
+        const uint32_t m0 = t * (uint32_t)ROWS;
+        const uint32_t m_end = min(m0 + (uint32_t)ROWS, M);
+        const Tile nxt = tile_of(next, true);
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        // one chunk of register set s (number cl of the tile's order): to LDS,
+        // ``reload`` the set, multiply
+        auto step = [&](uint32_t cl, int s, auto &&reload) __attribute__((always_inline)) {
+            __syncthreads();  // the previous chunk's MFMAs have read the LDS
+#pragma unroll
+            for (int q = 0; q < WL; ++q)
+                *reinterpret_cast<u32x4 *>(&s_w[w_r + (uint32_t)q * kRowStep][w_sl * 16u]) = ws[s][q];
+#pragma unroll
+            for (int q = 0; q < (XA ? 0 : XL); ++q) {
+                const uint32_t L = (uint32_t)q * kMfmaThreads + threadIdx.x;
+                *reinterpret_cast<u32x4 *>(&s_x[L / kMfmaChunkSlices][(L % kMfmaChunkSlices) * 16u]) = xs[s][q];
+            }
+            __syncthreads();
+            reload();
+            if (!XA || cl < n_chunks) {
+                const uint32_t cx = chunk_at(cl, cur.rot);
+#pragma unroll
+                for (int i = 0; i < kMfmaStepsPerWave; ++i) {
+                    const uint32_t at = (wave * (uint32_t)kMfmaStepsPerWave + (uint32_t)i) * 64u + grp * 16u;
+                    const u32x4 a = *reinterpret_cast<const u32x4 *>(&s_w[rl & (uint32_t)(ROWS - 1)][at]);
+                    const u32x4 bx =
+                        XA ? *reinterpret_cast<const u32x4 *>(&s_xa[rl & (uint32_t)(XB - 1)][XA ? cx * kMfmaChunk + at : 0u])
+                           : *reinterpret_cast<const u32x4 *>(&s_x[XA ? 0u : (rl & (uint32_t)(XB - 1))][XA ? 0u : at]);
+                    acc = mfma16x16x32<DT>(rl < (uint32_t)ROWS ? a : z, rl < (uint32_t)XB ? bx : z, acc);
+                }
+            }
+        };
+        for (uint32_t c = 0; c < n_chunks; c += (uint32_t)kMfmaSets) {
+            // the tile's last two chunks load the next tile's first two;
+            // the choice is made on the resources, so that the loop has
+            // no branch around a load
+            const bool last = c + (uint32_t)kMfmaSets >= n_chunks;
+#pragma unroll
+            for (int s = 0; s < kMfmaSets; ++s)
+                step(c + (uint32_t)s, s, [&]() __attribute__((always_inline)) {
+                    const uint32_t k = chunk_at(last ? (uint32_t)s : c + (uint32_t)(kMfmaSets + s),
+                                                last ? nxt.rot : cur.rot);
+#pragma unroll
+                    for (int q = 0; q < WL; ++q)
+                        ws[s][q] = buf_load_nt(row_rsrc(last ? nxt.at[q] : cur.at[q],
+                                                        last ? nxt.on[q] : cur.on[q], row_bytes),
+                                               k * kMfmaChunk + w_sl * 16u);
+                    load_x(k, xs[s]);
+                });
+        }
+        cur = nxt;
+        s_red[wave][lane] = acc;
+        __syncthreads();
+        // (s_red is written again only after the next tile's barriers)
+        if (wave == 0) {
+            f32x4 v = s_red[0][lane];
+#pragma unroll
+            for (int w = 1; w < kMfmaWaves; ++w) {
+                const f32x4 o = s_red[w][lane];
+                v.x += o.x;
+                v.y += o.y;
+                v.z += o.z;
+                v.w += o.w;
+            }
+            if (rl < nb) {
+                const float vals[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t m = m0 + grp * 4u + (uint32_t)i;
+                    if (m < m_end)
+                        y[(uint64_t)rl * M + m] = vals[i];
+                }
+            }
+        }
+    };
+    static_tile_stream(g, n_tiles, prime, prologue, body, NoOp());
+    if (pro_err)
+        raise_flag(g.err, pro_err);
+}
+
 typedef void (*GemvKernel)(const uint8_t *, const uint32_t *, uint64_t, uint32_t, uint32_t,
                            const uint8_t *, uint32_t, float *, uint32_t, uint32_t, Gate);
 
@@ -960,6 +1142,32 @@ static GemvKernel plan_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype
     }
 }
 
+// The streaming form of an MFMA plan's kernel, under the static schedule, for
+// rows that never cross pages (a page holds a whole number of them) and a W
+// whose table its LDS holds, where workgroups (two per CU) take more than one
+// tile: with x for the whole K in LDS, more than two (11008 x 4096 batch 4 on
+// 192 CUs, four calls: 87.4 us by tiles, 88.7 streaming; on 128 CUs 122.8 and
+// 119.2).  With one tile each there is no tile end to run over (4096 x 8192
+// batch 8: 63.1 and 65.5 us).
+template <int DT>
+static GemvKernel stream_kernel_dt(const sgdrc_gemv_plan &p)
+{
+    if (p.batch_cols == 4 && p.x_once)
+        return p.rows == 16 ? k_gemm_stream<DT, 16, 4, true> : k_gemm_stream<DT, 8, 4, true>;
+    if (p.batch_cols == 4)
+        return p.rows == 16 ? k_gemm_stream<DT, 16, 4, false> : k_gemm_stream<DT, 8, 4, false>;
+    return p.rows == 16 ? k_gemm_stream<DT, 16, 8, false> : k_gemm_stream<DT, 8, 8, false>;
+}
+
+static GemvKernel stream_kernel(const sgdrc_gemv_plan &p, int w_dtype, uint64_t row_bytes,
+                                uint64_t w_pages, uint64_t page_bytes, int allowed)
+{
+    if (p.path != SGDRC_GEMV_MFMA || w_pages > (uint64_t)kPtCap || page_bytes % row_bytes ||
+        p.tiles <= (p.x_once ? 4u : 2u) * (uint64_t)allowed)
+        return nullptr;
+    return w_dtype == SGDRC_BF16 ? stream_kernel_dt<SGDRC_BF16>(p) : stream_kernel_dt<SGDRC_F16>(p);
+}
+
 static int kernel_occupancy(GemvKernel k, int threads)
 {
     static std::mutex mu;
@@ -1055,7 +1263,9 @@ int colored_gemv(sgdrc_ctx *ctx, const sgdrc_paged *w, int w_dtype, uint32_t M, 
     const uint64_t w_pages = ((uint64_t)M * row_bytes + (1ull << page_shift) - 1u) >> page_shift;
     GemvKernel k = g.statics ? ring_kernel(plan, w_dtype, x_dtype, row_bytes, w_pages, 1ull << page_shift) : nullptr;
     const bool ring = k != nullptr;
-    if (!ring)
+    if (!ring && g.statics)
+        k = stream_kernel(plan, w_dtype, row_bytes, w_pages, 1ull << page_shift, li.allowed);
+    if (!k)
         k = plan_kernel(plan, w_dtype, x_dtype);
     if (!k)
         return set_error(SGDRC_EINVAL, "no kernel for the plan (library fault)");
