@@ -1027,6 +1027,16 @@ static sgdrc_gemv_plan make_plan(uint32_t allowed, int w_dtype, uint32_t M, uint
         p.batch_cols = batch <= 1 ? 1u : batch <= 2 ? 2u : batch <= 4 ? 4u : 8u;
         p.rows = 4u;
         p.loads = long_rows && batch <= 2 ? 3u : 2u;
+        // wide batches hold x of every batch row per slice in flight: with
+        // one slice (8 columns; 4 when an element of x is wider than one of W)
+        // twice the wavefronts fit, which wins as soon as a CU has more than
+        // one tile.  MI355X, four calls, two slices / one: bf16 W with fp32 x,
+        // 11008 x 4096 batch 5 on 256 CUs 260.9 / 148.1 us, batch 3 112.0 /
+        // 93.6, 4096 x 8192 batch 8 on 64 CUs 587.1 / 365.9; fp32, 4096 x 4096
+        // batch 8 93.3 / 88.7, 1000 x 2000 (one tile per CU) 31.2 / 33.3.
+        const bool x_wider = dtype_size(x_dtype) > dtype_size(w_dtype);
+        if ((M + 3u) / 4u > a && (p.batch_cols == 8u || (p.batch_cols == 4u && x_wider)))
+            p.loads = 1u;
         const bool one_round6 = w_dtype == x_dtype && kv <= 6u * (uint64_t)kGemvThreads;
         if (batch <= 1 && long_rows && (few || one_round6)) {
             p.rows = 2u;
@@ -1070,6 +1080,10 @@ static GemvKernel valu_kernel(const sgdrc_gemv_plan &p)
     SGDRC_VALU(2, 4, 2, false)
     SGDRC_VALU(4, 4, 2, false)
     SGDRC_VALU(8, 4, 2, false)
+    SGDRC_VALU(8, 4, 1, false)
+    if constexpr (Dt<XT>::size > Dt<WT>::size) {
+        SGDRC_VALU(4, 4, 1, false)
+    }
     if constexpr (WT == XT) {  // x once per workgroup: one type only
         SGDRC_VALU(1, 2, 6, true)
         SGDRC_VALU(2, 4, 3, true)
