@@ -312,11 +312,13 @@ __device__ __forceinline__ uint64_t tile_phys(const uint8_t *w_pool, uint32_t en
 // (s_red alternates).  The sums and their order are those of the kernel
 // above: the same bits.  Every row is read through a buffer resource of its
 // own; the few that cross into another page are summed from per-slice lookups
-// at their turn, which empties the ring, so pages hold at least
-// kRingRowsPerPage rows (64 KiB pages, 6000-byte rows: 47.8 against 42.8 us
-// for four calls).  The entries of W's whole table are staged in LDS (at most
-// kRingPages); the first tile's is read directly so that its loads start
-// before the staging ends.
+// at their turn, which empties the ring, so pages hold a whole number of rows
+// or at least kRingRowsPerPage (64 KiB pages, 6000-byte rows: 47.8 against
+// 42.8 us for four calls).  A row's page-table entry is the same for the whole
+// wavefront: a scalar load, made a row ahead; no table is staged (the 1376
+// entries of 90 MB in 64 KiB pages, staged per workgroup, cost 1.1 us a call:
+// 11008 x 4096, four calls, batch 1 63.2 against 67.9 us, tile loop 67.8; batch
+// 2 67.8, 74.3 and 73.8).
 //
 // HBM-bound: bf16, batch 1, 2 MiB pages, 12 rotated copies, on MI355X, four
 // calls in a row, tile loop / ring: 4096 x 11008 on 256 CUs 68.3 / 64.7 us, on
@@ -324,7 +326,6 @@ __device__ __forceinline__ uint64_t tile_phys(const uint8_t *w_pool, uint32_t en
 // 72.6 / 64.6; batch 2, 11008 x 4096 on 64 CUs 172.0 / 156.5, on 256 CUs 69.5 /
 // 69.0.  (A plain read of 90 MB takes 14.1 us a launch.)  Three workgroups per
 // CU were up to 26 percent slower on 64 CUs, six or eight up to 8 percent.
-constexpr uint32_t kRingPages = 2048;
 constexpr int kRingWgsPerCu = 5;
 constexpr uint64_t kRingRowsPerPage = 32;
 
@@ -337,14 +338,12 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
     constexpr int WSZ = Dt<WT>::size, XSZ = Dt<XT>::size;
     constexpr int EPV = 16 / WSZ;
     constexpr int XW = EPV * XSZ / 4;
-    __shared__ uint32_t s_pt[kRingPages];
     __shared__ float s_red[2][kGemvWaves][R * NB];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     const uint32_t row_bytes = K * (uint32_t)WSZ;  // at most U * 4 KiB
     const uint32_t KV = row_bytes / 16u;
     const uint64_t pmask = (1ull << shift) - 1ull;
-    const uint32_t w_pages = (uint32_t)(((uint64_t)M * row_bytes + pmask) >> shift);
-    uint32_t pro_err = 0u;
+    uint32_t bad = 0u;
 
     // x of this lane's slices for every batch row (zeros out of range)
     auto load_x = [&](uint32_t (&xs)[U][NB][XW]) __attribute__((always_inline)) {
@@ -383,14 +382,13 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
         Rsrc r;
         bool split;
     };
-    auto row_of = [&](uint32_t m, bool staged) __attribute__((always_inline)) {
+    auto row_of = [&](uint32_t m) __attribute__((always_inline)) {
         Row w;
         const uint64_t at = (uint64_t)m * row_bytes;
         const uint64_t p0 = at >> shift;
         w.split = m < M && p0 != (at + row_bytes - 1u) >> shift;
         const uint32_t j = m < M ? (uint32_t)p0 : 0u;
-        const uint32_t raw = staged ? s_pt[j] : pt[j];
-        const uint32_t e = __builtin_amdgcn_readfirstlane((uint64_t)raw < pool_pages ? raw : kBadPage);
+        const uint32_t e = __builtin_amdgcn_readfirstlane(checked_page(pt, j, pool_pages, bad));
         w.r = row_rsrc(tile_phys(w_pool, e, at, shift, pmask), m < M && !w.split && e != kBadPage, row_bytes);
         return w;
     };
@@ -399,7 +397,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
         u32x4 v = {0u, 0u, 0u, 0u};
         if (kv < KV) {
             const uint64_t off = (uint64_t)m * row_bytes + (uint64_t)kv * 16u;
-            const uint32_t p = s_pt[off >> shift];
+            const uint32_t p = checked_page(pt, off >> shift, pool_pages, bad);
             if (p != kBadPage)
                 v = load_nt(w_pool + ((uint64_t)p << shift) + (off & pmask));
         }
@@ -430,7 +428,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
     uint32_t ph = 0u;
     bool split = false;  // the row whose loads are in the ring
     auto prime = [&](uint32_t t) __attribute__((always_inline)) {
-        const Row w = row_of(t < n_tiles ? t * R : M, false);
+        const Row w = row_of(t < n_tiles ? t * R : M);
         split = w.split;
         // x first: loads complete in order, so that the loop's first use of
         // x does not wait for W
@@ -442,16 +440,12 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
             wv[u] = buf_load_nt(w.r, off0 + (uint32_t)u * kGemvThreads * 16u);
         }
     };
-    auto prologue = [&]() __attribute__((always_inline)) {
-        for (uint32_t i = threadIdx.x; i < w_pages; i += kGemvThreads)
-            s_pt[i] = checked_page(pt, i, pool_pages, pro_err);
-    };
     auto body = [&](uint32_t t, uint32_t next, uint32_t, uint32_t &) __attribute__((always_inline)) {
         const uint32_t m0 = t * R;
         uint32_t xn[XO ? 1 : U][XO ? 1 : NB][XO ? 1 : XW];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const Row nxt = row_of(r + 1 < R ? m0 + r + 1u : next < n_tiles ? next * R : M, true);
+            const Row nxt = row_of(r + 1 < R ? m0 + r + 1u : next < n_tiles ? next * R : M);
             // x of the next tile, before that tile's first loads of W
             if constexpr (!XO) {
                 if (r + 1 == R)
@@ -504,9 +498,9 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
                         xk[u][b][i] = xn[u][b][i];
         }
     };
-    static_tile_stream(g, n_tiles, prime, prologue, body, NoOp());
-    if (pro_err)
-        raise_flag(g.err, pro_err);
+    static_tile_stream(g, n_tiles, prime, NoOp(), body, NoOp());
+    if (bad)
+        raise_flag(g.err, bad);
 }
 
 template <int DT>
@@ -779,12 +773,13 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
 }
 
 // The same GEMM under the static schedule for a W whose rows do not cross
-// pages and whose table fits in LDS: the chunk loads run on over tile ends.  The kernel above ends a tile with pad
+// pages: the chunk loads run on over tile ends.  The kernel above ends a tile with pad
 // chunks (nothing in flight) and fills its two register sets again for the
 // next; here the last two chunks of a tile load the first two of the
 // workgroup's next tile, and the sum over the waves overlaps them.  Same
 // chunks in the same order per output: the same bits.  Rows are read through
-// a buffer resource each, also where a tile spans pages.
+// a buffer resource each, also where a tile spans pages; their page-table
+// entries are scalar loads, made a tile ahead.
 //
 // HBM-bound with the x staging beside it: bf16, 11008 x 4096 in 2 MiB pages, four
 // calls with 12 rotated copies on MI355X, by tiles / streaming: batch 8 on 256
@@ -796,7 +791,6 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
     uint32_t M, uint32_t K, const uint8_t *__restrict__ x, uint32_t nb, float *__restrict__ y,
     uint32_t shift, uint32_t n_tiles, Gate g)
 {
-    __shared__ uint32_t s_pt[kPtCap];
     __shared__ f32x4 s_red[kMfmaWaves][64];
     constexpr int WL = ROWS * (int)kMfmaChunkSlices / kMfmaThreads;  // W loads per lane
     constexpr int XL = XB * (int)kMfmaChunkSlices / kMfmaThreads;    // x loads per lane
@@ -812,9 +806,8 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
     const uint32_t KV = row_bytes / 16u;
     const uint32_t n_chunks = (KV + kMfmaChunkSlices - 1u) / kMfmaChunkSlices;
     const uint64_t pmask = (1ull << shift) - 1ull;
-    const uint64_t w_pages = ((uint64_t)M * row_bytes + pmask) >> shift;  // at most kPtCap
     const Rsrc x_rsrc = make_rsrc(x, nb * row_bytes);
-    uint32_t pro_err = 0u;
+    uint32_t bad = 0u;
     const uint32_t w_sl = threadIdx.x % kMfmaChunkSlices;
     const uint32_t w_r = __builtin_amdgcn_readfirstlane(threadIdx.x / kMfmaChunkSlices);
     u32x4 ws[kMfmaSets][WL], xs[kMfmaSets][XL];
@@ -825,7 +818,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         bool on[WL];      // whether there is anything to read
         uint32_t rot;
     };
-    auto tile_of = [&](uint32_t t, bool staged) __attribute__((always_inline)) {
+    auto tile_of = [&](uint32_t t) __attribute__((always_inline)) {
         Tile d;
         const uint32_t m0 = t < n_tiles ? t * (uint32_t)ROWS : M;
         d.rot = (m0 / 16u) % n_chunks;
@@ -833,8 +826,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         for (int q = 0; q < WL; ++q) {
             const uint32_t m = m0 + w_r + (uint32_t)q * kRowStep;
             const uint64_t at = (uint64_t)(m < M ? m : 0u) * row_bytes;
-            const uint32_t raw = staged ? s_pt[at >> shift] : pt[at >> shift];
-            const uint32_t e = __builtin_amdgcn_readfirstlane((uint64_t)raw < pool_pages ? raw : kBadPage);
+            const uint32_t e = __builtin_amdgcn_readfirstlane(checked_page(pt, at >> shift, pool_pages, bad));
             d.at[q] = tile_phys(w_pool, e, at, shift, pmask);
             d.on[q] = m < M && e != kBadPage;
         }
@@ -861,13 +853,12 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
     };
     Tile cur;
     auto prime = [&](uint32_t t) __attribute__((always_inline)) {
-        cur = tile_of(t, false);
+        cur = tile_of(t);
 #pragma unroll
         for (int s = 0; s < kMfmaSets; ++s)
             load_rows(cur, chunk_at((uint32_t)s, cur.rot), s);
     };
     auto prologue = [&]() __attribute__((always_inline)) {
-        stage_whole_table(pt, pool_pages, w_pages, s_pt, pro_err);
         if (XA) {
             constexpr uint32_t kSl = kXaBytes / 16u;
 #pragma unroll
@@ -882,7 +873,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
     auto body = [&](uint32_t t, uint32_t next, uint32_t, uint32_t &) __attribute__((always_inline)) {
         const uint32_t m0 = t * (uint32_t)ROWS;
         const uint32_t m_end = min(m0 + (uint32_t)ROWS, M);
-        const Tile nxt = tile_of(next, true);
+        const Tile nxt = tile_of(next);
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
         const u32x4 z = {0u, 0u, 0u, 0u};
         // one chunk of register set s (number cl of the tile's order): to LDS,
@@ -956,8 +947,8 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         }
     };
     static_tile_stream(g, n_tiles, prime, prologue, body, NoOp());
-    if (pro_err)
-        raise_flag(g.err, pro_err);
+    if (bad)
+        raise_flag(g.err, bad);
 }
 
 typedef void (*GemvKernel)(const uint8_t *, const uint32_t *, uint64_t, uint32_t, uint32_t,
@@ -1094,15 +1085,14 @@ static GemvKernel valu_kernel(const sgdrc_gemv_plan &p)
 }
 
 // The ring kernel of a vector plan whose rows one round of loads covers, for
-// W and x of one type and a table that its LDS holds; launched under the
-// static schedule only (the queues name a tile too late to load ahead).  Its
+// W and x of one type; launched under the static schedule only (the queues name a tile too late to load ahead).  Its
 // ring has as many loads as a row needs (the plan's ``loads`` at most).
 static GemvKernel ring_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype, uint64_t row_bytes,
-                              uint64_t w_pages, uint64_t page_bytes)
+                              uint64_t page_bytes)
 {
     const uint64_t slots = (row_bytes + kGemvThreads * 16u - 1u) / (kGemvThreads * 16u);
-    if (p.path != SGDRC_GEMV_VALU || w_dtype != x_dtype || w_pages > kRingPages || slots > p.loads ||
-        row_bytes * kRingRowsPerPage > page_bytes)
+    if (p.path != SGDRC_GEMV_VALU || w_dtype != x_dtype || slots > p.loads ||
+        (page_bytes % row_bytes && row_bytes * kRingRowsPerPage > page_bytes))
         return nullptr;
 #define SGDRC_RING(NB, R, U, XO)                                                       \
     if (p.batch_cols == NB && p.rows == R && slots == U && p.x_once == (XO ? 1u : 0u)) { \
@@ -1157,9 +1147,8 @@ static GemvKernel plan_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype
 }
 
 // The streaming form of an MFMA plan's kernel, under the static schedule, for
-// rows that never cross pages (a page holds a whole number of them) and a W
-// whose table its LDS holds, where workgroups (two per CU) take more than one
-// tile: with x for the whole K in LDS, more than two (11008 x 4096 batch 4 on
+// rows that never cross pages (a page holds a whole number of them), where
+// workgroups (two per CU) take more than one tile: with x for the whole K in LDS, more than two (11008 x 4096 batch 4 on
 // 192 CUs, four calls: 87.4 us by tiles, 88.7 streaming; on 128 CUs 122.8 and
 // 119.2).  With one tile each there is no tile end to run over (4096 x 8192
 // batch 8: 63.1 and 65.5 us).
@@ -1174,9 +1163,9 @@ static GemvKernel stream_kernel_dt(const sgdrc_gemv_plan &p)
 }
 
 static GemvKernel stream_kernel(const sgdrc_gemv_plan &p, int w_dtype, uint64_t row_bytes,
-                                uint64_t w_pages, uint64_t page_bytes, int allowed)
+                                uint64_t page_bytes, int allowed)
 {
-    if (p.path != SGDRC_GEMV_MFMA || w_pages > (uint64_t)kPtCap || page_bytes % row_bytes ||
+    if (p.path != SGDRC_GEMV_MFMA || page_bytes % row_bytes ||
         p.tiles <= (p.x_once ? 4u : 2u) * (uint64_t)allowed)
         return nullptr;
     return w_dtype == SGDRC_BF16 ? stream_kernel_dt<SGDRC_BF16>(p) : stream_kernel_dt<SGDRC_F16>(p);
@@ -1274,11 +1263,10 @@ int colored_gemv(sgdrc_ctx *ctx, const sgdrc_paged *w, int w_dtype, uint32_t M, 
     if (rc)
         return rc;
     const uint64_t row_bytes = (uint64_t)K * dtype_size(w_dtype);
-    const uint64_t w_pages = ((uint64_t)M * row_bytes + (1ull << page_shift) - 1u) >> page_shift;
-    GemvKernel k = g.statics ? ring_kernel(plan, w_dtype, x_dtype, row_bytes, w_pages, 1ull << page_shift) : nullptr;
+    GemvKernel k = g.statics ? ring_kernel(plan, w_dtype, x_dtype, row_bytes, 1ull << page_shift) : nullptr;
     const bool ring = k != nullptr;
     if (!ring && g.statics)
-        k = stream_kernel(plan, w_dtype, row_bytes, w_pages, 1ull << page_shift, li.allowed);
+        k = stream_kernel(plan, w_dtype, row_bytes, 1ull << page_shift, li.allowed);
     if (!k)
         k = plan_kernel(plan, w_dtype, x_dtype);
     if (!k)
