@@ -392,15 +392,15 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
         w.r = row_rsrc(tile_phys(w_pool, e, at, shift, pmask), m < M && !w.split && e != kBadPage, row_bytes);
         return w;
     };
-    auto split_row = [&](uint32_t m, int u) __attribute__((always_inline)) {
+    // one slice of a row that lies on two pages, with entries e0 and e1
+    auto split_slice = [&](uint32_t m, int u, uint32_t e0, uint32_t e1) __attribute__((always_inline)) {
         const uint32_t kv = (uint32_t)u * kGemvThreads + threadIdx.x;
         u32x4 v = {0u, 0u, 0u, 0u};
-        if (kv < KV) {
-            const uint64_t off = (uint64_t)m * row_bytes + (uint64_t)kv * 16u;
-            const uint32_t p = checked_page(pt, off >> shift, pool_pages, bad);
-            if (p != kBadPage)
-                v = load_nt(w_pool + ((uint64_t)p << shift) + (off & pmask));
-        }
+        const uint64_t at = (uint64_t)m * row_bytes;
+        const uint64_t off = at + (uint64_t)kv * 16u;
+        const uint32_t p = off >> shift == at >> shift ? e0 : e1;
+        if (kv < KV && p != kBadPage)
+            v = load_nt(w_pool + ((uint64_t)p << shift) + (off & pmask));
         return v;
     };
     auto add_slice = [&](const u32x4 &w, uint32_t (&xs)[NB][XW], float (&acc)[NB]) __attribute__((always_inline)) {
@@ -462,9 +462,16 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (split) {  // the ring held zeros for it
+                // its two entries are scalar loads too: a vector load of an
+                // entry a slice made the slices' round trips follow each other
+                // (4096 x 11008 in 2 MiB pages, four calls: 74.1
+                // against 63.9 us)
+                const uint64_t j = (uint64_t)(m0 + r) * row_bytes >> shift;
+                const uint32_t e0 = __builtin_amdgcn_readfirstlane(checked_page(pt, j, pool_pages, bad));
+                const uint32_t e1 = __builtin_amdgcn_readfirstlane(checked_page(pt, j + 1u, pool_pages, bad));
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    add_slice(split_row(m0 + r, u), xk[u], acc);
+                    add_slice(split_slice(m0 + r, u, e0, e1), xk[u], acc);
             }
             split = nxt.split;
 #pragma unroll
@@ -773,9 +780,9 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
 }
 
 // The same GEMM under the static schedule for a W whose rows do not cross
-// pages: the chunk loads run on over tile ends.  The kernel above ends a tile with pad
-// chunks (nothing in flight) and fills its two register sets again for the
-// next; here the last two chunks of a tile load the first two of the
+// pages: the chunk loads run on over tile ends.  The kernel above ends a tile
+// with pad chunks (nothing in flight) and fills its two register sets again for
+// the next; here the last two chunks of a tile load the first two of the
 // workgroup's next tile, and the sum over the waves overlaps them.  Same
 // chunks in the same order per output: the same bits.  Rows are read through
 // a buffer resource each, also where a tile spans pages; their page-table
@@ -1085,8 +1092,9 @@ static GemvKernel valu_kernel(const sgdrc_gemv_plan &p)
 }
 
 // The ring kernel of a vector plan whose rows one round of loads covers, for
-// W and x of one type; launched under the static schedule only (the queues name a tile too late to load ahead).  Its
-// ring has as many loads as a row needs (the plan's ``loads`` at most).
+// W and x of one type; launched under the static schedule only (the queues
+// name a tile too late to load ahead).  Its ring has as many loads as a row
+// needs (the plan's ``loads`` at most).
 static GemvKernel ring_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype, uint64_t row_bytes,
                               uint64_t page_bytes)
 {
@@ -1148,9 +1156,9 @@ static GemvKernel plan_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype
 
 // The streaming form of an MFMA plan's kernel, under the static schedule, for
 // rows that never cross pages (a page holds a whole number of them), where
-// workgroups (two per CU) take more than one tile: with x for the whole K in LDS, more than two (11008 x 4096 batch 4 on
-// 192 CUs, four calls: 87.4 us by tiles, 88.7 streaming; on 128 CUs 122.8 and
-// 119.2).  With one tile each there is no tile end to run over (4096 x 8192
+// workgroups (two per CU) take more than one tile: with x for the whole K in
+// LDS, more than two (11008 x 4096 batch 4 on 192 CUs, four calls: 87.4 us by
+// tiles, 88.7 streaming; on 128 CUs 122.8 and 119.2).  With one tile each there is no tile end to run over (4096 x 8192
 // batch 8: 63.1 and 65.5 us).
 template <int DT>
 static GemvKernel stream_kernel_dt(const sgdrc_gemv_plan &p)

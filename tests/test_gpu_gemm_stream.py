@@ -28,7 +28,9 @@ def ctx():
 # (M, K, batch, dtype, page shift); K * 2 divides the page
 CASES = [(1301, 4096, 8, sg.BF16, 17), (2900, 4096, 4, sg.BF16, 21), (1111, 2048, 6, sg.F16, 16),
          (1040, 8192, 5, sg.F16, 18), (2100, 256, 3, sg.BF16, 12), (1200, 16384, 4, sg.BF16, 19),
-         (4000, 1024, 8, sg.BF16, 16), (1050, 8, 8, sg.F16, 10)]
+         (4000, 1024, 8, sg.BF16, 16), (1050, 8, 8, sg.F16, 10),
+         # one row a page: more entries than a tile stages
+         (1100, 4096, 8, sg.BF16, 13), (1050, 8192, 4, sg.F16, 14)]
 
 
 @pytest.mark.parametrize("M,K,B,dt,shift", CASES)

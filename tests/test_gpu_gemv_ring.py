@@ -1,8 +1,9 @@
 """Batch 1-2 GEMV under the static schedule (the ring kernel: the next rows'
 loads stay in flight) against the oracle and, bit for bit, against the queue
 schedule (a partial mask; the tile loop): every ring length, rows that cross a
-page end, row and slice remainders, more and fewer tiles than workgroups, and
-a page-table entry outside the pool."""
+page end, row and slice remainders, more and fewer tiles than workgroups, small
+pages of one or a few whole rows, tables of more than 2048 entries, and
+page-table entries outside the pool."""
 import sys
 
 import numpy as np
@@ -30,7 +31,10 @@ def ctx():
 CASES = [(1, 2048, 1, BF16, 21), (5, 8, 1, BF16, 16), (1031, 2056, 1, F16, 18), (2500, 4096, 1, BF16, 21),
          (333, 4104, 1, BF16, 19), (701, 6144, 1, F16, 20), (411, 8184, 1, BF16, 21),
          (300, 5120, 1, F32, 20), (513, 11008, 1, BF16, 21), (97, 12288, 1, F16, 21),
-         (2049, 4096, 2, BF16, 21), (700, 6136, 2, F16, 19), (1025, 1024, 2, F32, 17), (259, 3072, 2, F32, 20)]
+         (2049, 4096, 2, BF16, 21), (700, 6136, 2, F16, 19), (1025, 1024, 2, F32, 17), (259, 3072, 2, F32, 20),
+         # a page holds one, two or eight whole rows
+         (2500, 4096, 1, BF16, 13), (1100, 8192, 1, F16, 14), (701, 2048, 1, F32, 14), (2100, 4096, 2, BF16, 13),
+         (1031, 4096, 2, F16, 16)]
 
 
 @pytest.mark.parametrize("M,K,B,dt,shift", CASES)
@@ -69,3 +73,25 @@ def test_ring_skips_a_bad_page(ctx, orc, bad):
     assert (ys[0] == ys[1]).all()
     rows = np.arange(M) * 2 * K >> shift
     assert (ys[0][rows == bad][:-1] == 0).all() and (ys[0][rows != bad] != 0).any()
+
+
+def test_ring_skips_bad_small_pages(ctx, orc):
+    """The same with a row a page: each page's entry is some wavefront's own."""
+    M, K, shift = 2060, 4096, 13
+    pool, pt, d_pool, d_pt, pool_pages = tp.upload_w(orc, M, K, BF16, shift, range(48), 9, 1, 6)
+    assert len(pt) == M
+    xb = tp.to_dev(tp.x_bits(BF16, K, 5))
+    for bad in (0, 1, 4, 1027, M - 1):
+        d_bad = d_pt.clone()
+        d_bad[bad] = pool_pages
+        ys = []
+        for cus in (None, list(range(40))):
+            y = torch.full((M,), 7.0, device=DEV)
+            ctx.device_error()
+            sg.set_cu_mask(ctx, None, cus)
+            sg.colored_gemv(ctx, sg.paged(d_pool, d_bad, pool_pages), BF16, M, K, xb, BF16, 1, y, shift)
+            sg.set_cu_mask(ctx, None, None)
+            assert ctx.device_error() & sg.DEVERR_PT_RANGE
+            ys.append(y.cpu().numpy())
+        assert (ys[0].view(np.uint32) == ys[1].view(np.uint32)).all()
+        assert ys[0][bad] == 0 and (np.delete(ys[0], bad) != 0).all()
