@@ -884,13 +884,17 @@ __device__ __forceinline__ void static_wave_loop(const Gate &g, uint32_t n_tiles
 
 // Page-table lookup with the range check every kernel applies: an entry
 // outside the pool yields kBadPage and sets kDevErrPtRange in ``err``.
-__device__ __forceinline__ uint32_t checked_page(const uint32_t *pt, uint64_t j,
-                                                 uint64_t pool_pages, uint32_t &err)
+__device__ __forceinline__ uint32_t checked_entry(uint32_t p, uint64_t pool_pages, uint32_t &err)
 {
-    const uint32_t p = pt[j];
     const bool bad = (uint64_t)p >= pool_pages;
     err |= bad ? kDevErrPtRange : 0u;
     return bad ? kBadPage : p;
+}
+
+__device__ __forceinline__ uint32_t checked_page(const uint32_t *pt, uint64_t j,
+                                                 uint64_t pool_pages, uint32_t &err)
+{
+    return checked_entry(pt[j], pool_pages, err);
 }
 
 // Buffer resources (gfx9 descriptor, raw addressing: stride 0, byte offsets,

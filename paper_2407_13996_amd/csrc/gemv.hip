@@ -786,12 +786,14 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
 // workgroup's next tile, and the sum over the waves overlaps them.  Same
 // chunks in the same order per output: the same bits.  Rows are read through
 // a buffer resource each, also where a tile spans pages; their page-table
-// entries are scalar loads, made a tile ahead.
+// entries are scalar loads, made when a tile begins and used in its last chunks.
 //
 // HBM-bound with the x staging beside it: bf16, 11008 x 4096 in 2 MiB pages, four
 // calls with 12 rotated copies on MI355X, by tiles / streaming: batch 8 on 256
-// CUs 76.9 / 71.6 us, 192 96.1 / 89.1, 128 139.5 / 126.7, 64 212.3 / 184.5; batch
-// 4 on 128 CUs 122.8 / 119.2, 64 175.4 / 164.6.
+// CUs 76.9 / 72.4 us (73.0 with the entries resolved where they are loaded; 71.5
+// with the whole table staged in LDS, which 64 KiB pages do not allow: 89.6
+// against 85.8 us there); with the staged table, 192 CUs 96.1 / 89.1, 128 139.5 /
+// 126.7, 64 212.3 / 184.5; batch 4 on 128 CUs 122.8 / 119.2, 64 175.4 / 164.6.
 template <int DT, int ROWS, int XB, bool XA>
 __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm_stream(
     const uint8_t *__restrict__ w_pool, const uint32_t *__restrict__ pt, uint64_t pool_pages,
@@ -825,7 +827,16 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         bool on[WL];      // whether there is anything to read
         uint32_t rot;
     };
-    auto tile_of = [&](uint32_t t) __attribute__((always_inline)) {
+    // (their page-table entries as the table holds them)
+    auto load_entries = [&](uint32_t t, uint32_t (&raw)[WL]) __attribute__((always_inline)) {
+        const uint32_t m0 = t < n_tiles ? t * (uint32_t)ROWS : M;
+#pragma unroll
+        for (int q = 0; q < WL; ++q) {
+            const uint32_t m = m0 + w_r + (uint32_t)q * kRowStep;
+            raw[q] = pt[(uint64_t)(m < M ? m : 0u) * row_bytes >> shift];
+        }
+    };
+    auto tile_of = [&](uint32_t t, const uint32_t (&raw)[WL]) __attribute__((always_inline)) {
         Tile d;
         const uint32_t m0 = t < n_tiles ? t * (uint32_t)ROWS : M;
         d.rot = (m0 / 16u) % n_chunks;
@@ -833,7 +844,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         for (int q = 0; q < WL; ++q) {
             const uint32_t m = m0 + w_r + (uint32_t)q * kRowStep;
             const uint64_t at = (uint64_t)(m < M ? m : 0u) * row_bytes;
-            const uint32_t e = __builtin_amdgcn_readfirstlane(checked_page(pt, at >> shift, pool_pages, bad));
+            const uint32_t e = __builtin_amdgcn_readfirstlane(checked_entry(raw[q], pool_pages, bad));
             d.at[q] = tile_phys(w_pool, e, at, shift, pmask);
             d.on[q] = m < M && e != kBadPage;
         }
@@ -860,7 +871,9 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
     };
     Tile cur;
     auto prime = [&](uint32_t t) __attribute__((always_inline)) {
-        cur = tile_of(t);
+        uint32_t raw[WL];
+        load_entries(t, raw);
+        cur = tile_of(t, raw);
 #pragma unroll
         for (int s = 0; s < kMfmaSets; ++s)
             load_rows(cur, chunk_at((uint32_t)s, cur.rot), s);
@@ -880,7 +893,9 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
     auto body = [&](uint32_t t, uint32_t next, uint32_t, uint32_t &) __attribute__((always_inline)) {
         const uint32_t m0 = t * (uint32_t)ROWS;
         const uint32_t m_end = min(m0 + (uint32_t)ROWS, M);
-        const Tile nxt = tile_of(next);
+        const uint32_t rot = cur.rot;
+        uint32_t raw[WL];  // used a tile's chunks later, so that nothing waits for it
+        load_entries(next, raw);
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
         const u32x4 z = {0u, 0u, 0u, 0u};
         // one chunk of register set s (number cl of the tile's order): to LDS,
@@ -898,7 +913,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
             __syncthreads();
             reload();
             if (!XA || cl < n_chunks) {
-                const uint32_t cx = chunk_at(cl, cur.rot);
+                const uint32_t cx = chunk_at(cl, rot);
 #pragma unroll
                 for (int i = 0; i < kMfmaStepsPerWave; ++i) {
                     const uint32_t at = (wave * (uint32_t)kMfmaStepsPerWave + (uint32_t)i) * 64u + grp * 16u;
@@ -912,23 +927,17 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         };
         for (uint32_t c = 0; c < n_chunks; c += (uint32_t)kMfmaSets) {
             // the tile's last two chunks load the next tile's first two;
-            // the choice is made on the resources, so that the loop has
-            // no branch around a load
+            // the choice is made on the rows, so that the loop has no branch
+            // around a vector load
             const bool last = c + (uint32_t)kMfmaSets >= n_chunks;
+            if (last)
+                cur = tile_of(next, raw);
 #pragma unroll
             for (int s = 0; s < kMfmaSets; ++s)
                 step(c + (uint32_t)s, s, [&]() __attribute__((always_inline)) {
-                    const uint32_t k = chunk_at(last ? (uint32_t)s : c + (uint32_t)(kMfmaSets + s),
-                                                last ? nxt.rot : cur.rot);
-#pragma unroll
-                    for (int q = 0; q < WL; ++q)
-                        ws[s][q] = buf_load_nt(row_rsrc(last ? nxt.at[q] : cur.at[q],
-                                                        last ? nxt.on[q] : cur.on[q], row_bytes),
-                                               k * kMfmaChunk + w_sl * 16u);
-                    load_x(k, xs[s]);
+                    load_rows(cur, chunk_at(last ? (uint32_t)s : c + (uint32_t)(kMfmaSets + s), cur.rot), s);
                 });
         }
-        cur = nxt;
         s_red[wave][lane] = acc;
         __syncthreads();
         // (s_red is written again only after the next tile's barriers)
