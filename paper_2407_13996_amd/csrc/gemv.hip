@@ -461,7 +461,12 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
                 wv[u] = buf_load_nt(nxt.r, off0 + (uint32_t)u * kGemvThreads * 16u);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (split) {  // the ring held zeros for it
+            if (split) {
+                // the ring held zeros for it, whose products with an infinite
+                // x are NaN: its sum begins anew
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    acc[b] = 0.0f;
                 // its two entries are scalar loads too: a vector load of an
                 // entry a slice made the slices' round trips follow each other
                 // (4096 x 11008 in 2 MiB pages, four calls: 74.1
