@@ -29,7 +29,12 @@
  *    colored_gemv enqueue kernels only (no memset, copy or host wait), and
  *    every per-launch value travels in the kernel arguments, so they may be
  *    captured into a HIP graph and replayed, except on a stream with an
- *    eviction flag (preemptible launches are resumed from the host).
+ *    eviction flag (preemptible launches are resumed from the host).  A
+ *    captured launch keeps the work queue of the stream that it was captured
+ *    on, wherever it is replayed: order replays with each other and with that
+ *    stream's launches, as launches on one stream are.  (Launches under the
+ *    static schedule, see set_cu_mask, use the queue for a classify's
+ *    histogram and the time log only; others may overlap.)
  *  - Page tables are arrays of uint32 pool-page indices.  Logical byte b of
  *    a paged tensor lives at pool + pt[b >> page_shift] * 2^page_shift +
  *    (b & (2^page_shift - 1)).  Kernels check every page-table entry
@@ -45,7 +50,8 @@
  *    a classify) and, on the ticket queues, any tiles left if no workgroup
  *    reached an allowed CU are handled by the grid's last workgroup, which
  *    may sit on any CU; under the static schedule (see set_cu_mask) the
- *    remainder of a relayout or triad is moved on an allowed CU.
+ *    remainder of a relayout, a triad or a classify without a histogram is
+ *    handled on an allowed CU.
  */
 #ifndef SGDRC_H
 #define SGDRC_H

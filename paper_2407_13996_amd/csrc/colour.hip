@@ -10,7 +10,8 @@
 // that each lane stores 16 consecutive colours per 16-byte store.  Tiles
 // cover the largest multiple of 16 addresses, through buffer ranges that end
 // there (so the tile body has no branch around its memory accesses); the
-// last n mod 16 addresses are coloured by the grid's last workgroup.
+// last n mod 16 addresses are coloured by the grid's last workgroup, or, in a
+// static launch without a histogram, by the first worker.
 //
 // The page-table build is an ordered stream compaction over the pool's page
 // addresses.  For most XOR hashes the rank of a run of pages is a product,
@@ -273,8 +274,8 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
             }
         }
     };
-    // runs in the last workgroup with every other workgroup's histogram in
-    // hist_acc: colour the last n mod 16 addresses, then publish the counts
+    // colour the last n mod 16 addresses, then, in the last workgroup with
+    // every other workgroup's histogram in hist_acc, publish the counts
     auto epilogue = [&]() {
         const uint64_t i = n16 + threadIdx.x;
         if (i < n) {
@@ -306,7 +307,7 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
         }
     };
     if (g.statics)
-        static_wave_loop(g, n_tiles, prologue, body, flush, epilogue);
+        static_wave_loop<HIST>(g, n_tiles, prologue, body, flush, epilogue);
     else
         gated_wave_loop(g, n_tiles, prologue, body, flush, epilogue);
 }
@@ -720,10 +721,9 @@ static int launch_classify(Ctx *c, const HashArgs &h, const TableArgs &tab,
         per_cu = std::min(occ[d_hist != nullptr], per_cu);
     }
     const uint32_t grid = gated_grid(c, per_cu, wg_tiles, li);
-    // the last n mod 16 addresses and the histogram's publication fall to the
-    // last workgroup (for 65536 addresses the call takes 7.2 us against 9.5
-    // with a kernel that follows the grid, for 2^26 the same)
-    g.arrive = g.statics && (d_hist || (n & 15u)) ? 1u : 0u;
+    // the histogram's publication falls to the last workgroup (for 65536
+    // addresses the call takes 7.2 us against 9.5 with a kernel that follows
+    // the grid, for 2^26 the same)
     hipLaunchKernelGGL(k, dim3(grid), dim3(kClsThreads), 0, s, d_addrs, n, d_colours, h, tab, acc,
                        d_hist, (uint32_t)n_tiles, g);
     SGDRC_HIP(hipGetLastError());

@@ -176,7 +176,6 @@ int make_gate(Ctx *c, void *stream, uint64_t n_tiles, int group_cus, Gate *g, La
     std::memcpy(g->xcd_rank, mi.rank, sizeof g->xcd_rank);
     g->n_allowed_xcd = mi.whole_xcds;
     g->n_xcd = (uint32_t)c->n_xcds;
-    g->arrive = 0u;
     g->xcc_allowed = mi.xcc_allowed;
     // queue groups: runs of 8 CUs inside each XCD, or one group (with a
     // static schedule no kernel reads them)

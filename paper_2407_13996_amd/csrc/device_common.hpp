@@ -105,7 +105,6 @@ struct Gate {
     uint8_t xcd_rank[kMaxXcds];
     uint32_t n_allowed_xcd;
     uint32_t n_xcd;
-    uint32_t arrive;             // static_wave_loop: 1 = the last workgroup runs the epilogue
 };
 
 // The testing aid of preemptible launches: whether tile ``tile`` is to be
@@ -837,10 +836,11 @@ __device__ __forceinline__ void gated_wave_loop(const Gate &g, uint32_t n_tiles,
 // as static_tile_loop): the workers are the wavefronts, numbered so that the
 // waves of one workgroup take consecutive tiles, and wave v of the W
 // workers takes tiles v, v + W, ...  ``flush`` runs once the workgroup's
-// waves are done.  With g.arrive the workgroups count their arrivals and the
-// last one runs ``epilogue``; without, there is no last workgroup and the host
-// enqueues whatever must follow the whole grid as a kernel of its own.
-template <typename Prologue, typename Body, typename Flush, typename Epilogue>
+// waves are done.  LAST: the workgroups count their arrivals and the last one
+// runs ``epilogue``, every flush complete.  Otherwise the epilogue needs no other
+// workgroup's result and runs in the first allowed one after its tiles, and
+// the launch shares nothing with others (replays of a captured one may overlap).
+template <bool LAST, typename Prologue, typename Body, typename Flush, typename Epilogue>
 __device__ __forceinline__ void static_wave_loop(const Gate &g, uint32_t n_tiles, Prologue prologue,
                                                  Body body, Flush flush, Epilogue epilogue)
 {
@@ -866,9 +866,13 @@ __device__ __forceinline__ void static_wave_loop(const Gate &g, uint32_t n_tiles
         }
         flush();
     }
-    if (g.arrive && arrive_last(g, &s_flag)) {
+    if (LAST) {
+        if (arrive_last(g, &s_flag)) {
+            epilogue();
+            reset_slot(g.q);
+        }
+    } else if (a == 0u && blockIdx.x < g.n_xcd) {
         epilogue();
-        reset_slot(g.q);
     }
     if (g.tlog) {
         __builtin_amdgcn_s_waitcnt(0);

@@ -1,5 +1,5 @@
-"""Classify's last workgroup under the static schedule (the last n mod 16
-addresses, the histogram): grids of one workgroup and more, with and without
+"""The end of a classify under the static schedule (the last n mod 16
+addresses, the histogram's last workgroup): grids of one workgroup and more, with and without
 a remainder, whole-XCD masks, every number of masks, two calls in a row (the
 accumulators and the arrival counters are clear again) and a queued launch
 between them.  Bit-exact against the oracle."""
@@ -45,3 +45,44 @@ def test_last_workgroup(ctx, orc, n, K, cus, hist):
         assert (got[:n] == ref).all() and (got[n:] == 0xEE).all()
         if hist:
             assert (d_hist.cpu().numpy().astype(np.uint64) == ref_hist).all()
+
+
+def test_overlapping_replays_without_histogram(ctx, orc):
+    """Two classifies without a histogram, captured on one stream and replayed
+    on two at once: the launches share no state, so every replay colours its
+    last n mod 16 addresses, and the stream's next histogram is right."""
+    n, K, rounds = (1 << 20) + 5, 6, 24
+    masks = synth.xor_masks(K, seed=K, min_bit=12)
+    cap = torch.cuda.Stream()
+    jobs = []
+    for seed in (1, 2):
+        addrs = synth.page_addresses(n, seed=seed)
+        ref, ref_hist = orc.classify(addrs, masks)
+        d_addrs = torch.from_numpy(addrs.view(np.int64)).to(DEV)
+        col = torch.full((n,), 0xEE, dtype=torch.uint8, device=DEV)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=cap):
+            sg.colour_classify(ctx, masks, d_addrs, col)
+        assert ctx.last_schedule(cap) == "static"
+        jobs.append((g, d_addrs, col, ref, ref_hist, torch.empty(rounds, 5, dtype=torch.uint8, device=DEV),
+                     torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    print(f"{rounds} replays of two captured classifies of {n} addresses on two streams", file=sys.stderr, flush=True)
+    for r in range(rounds):
+        for g, _, col, _, _, tails, st in jobs:
+            with torch.cuda.stream(st):
+                g.replay()
+                tails[r].copy_(col[-5:])
+                col[-5:].fill_(0xEE)
+    torch.cuda.synchronize()
+    for g, d_addrs, col, ref, ref_hist, tails, _ in jobs:
+        assert (col[:-5].cpu().numpy() == ref[:-5]).all()
+        assert (tails.cpu().numpy() == ref[-5:]).all()
+        d_hist = torch.full((1 << K,), 9, dtype=torch.int64, device=DEV)
+        sg.colour_classify(ctx, masks, d_addrs, col, d_hist, cap)
+        torch.cuda.synchronize()
+        assert (d_hist.cpu().numpy().astype(np.uint64) == ref_hist).all()
+    del jobs, g
+    torch.cuda.synchronize()
+    sg.stream_release(ctx, cap)
