@@ -612,14 +612,15 @@ __device__ __forceinline__ void gated_tile_loop(const Gate &g, uint32_t n_tiles,
 // counter.  With A allowed XCDs and W workgroups per XCD, the workgroup of
 // rank r on the allowed XCD of rank a is worker v = r A + a of W A, and
 // takes tiles v, v + W A, ... -- consecutive tiles on different XCDs, as a
-// plain grid would place them.  Workgroups on other XCDs leave at once.
+// plain grid would place them.  Workgroups on other XCDs take none and leave.
 // With a time log, workgroup 0 stamps the start and every workgroup, once
 // its stores are done, raises partial end stamp blockIdx mod kTimePartials
 // to its end time; the host reduces the partials with k_tlog_reduce after
-// the launch.  A workgroup on an allowed XCD runs ``prime`` with its first
-// tile (for loads that need not wait for the opening barrier), every workgroup
-// runs ``prologue``, and ``body(tile, next, cu, err)`` runs for each of the
-// workgroup's tiles with the tile it takes after that (n_tiles or more: none);
+// the launch.  Every workgroup runs ``prime`` with its first tile (n_tiles or
+// more if it has none, as on an XCD outside the mask, whose L2 is another
+// stream's: prime then reads no operand) for loads that need not wait for the
+// opening barrier, and ``prologue``; ``body(tile, next, cu, err)`` runs for each
+// of its tiles with the tile it takes after that (n_tiles or more: none);
 // ``tail``, work that needs no other tile's result, runs once, in worker 0
 // after its tiles.
 template <typename Prime, typename Prologue, typename Body, typename Tail>

@@ -345,8 +345,12 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
     const uint64_t pmask = (1ull << shift) - 1ull;
     uint32_t bad = 0u;
 
-    // x of this lane's slices for every batch row (zeros out of range)
-    auto load_x = [&](uint32_t (&xs)[U][NB][XW]) __attribute__((always_inline)) {
+    // x of this lane's slices for every batch row (zeros out of range, and
+    // wholly for a workgroup without tiles: one outside the mask reads no x
+    // through its XCD's L2.  A branch around prime, or leaving before it, cost
+    // the others 0.4 to 2.8 percent of a call, this nothing)
+    auto load_x = [&](uint32_t (&xs)[U][NB][XW], bool tiles) __attribute__((always_inline)) {
+        const uint32_t KX = tiles ? KV : 0u;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t kv = (uint32_t)u * kGemvThreads + threadIdx.x;
@@ -355,7 +359,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
 #pragma unroll
                 for (int i = 0; i < XW; ++i)
                     xs[u][b][i] = 0u;
-                if (kv < KV && (uint32_t)b < nb) {
+                if (kv < KX && (uint32_t)b < nb) {
                     const uint8_t *xp = x + ((uint64_t)b * K + (uint64_t)kv * EPV) * XSZ;
                     if (XW == 2) {
                         u32x2 v = *reinterpret_cast<const u32x2 *>(xp);
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
         split = w.split;
         // x first: loads complete in order, so that the loop's first use of
         // x does not wait for W
-        load_x(xk);
+        load_x(xk, t < n_tiles);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             // in the order of use, which the loop's waits count on
@@ -449,7 +453,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
             // x of the next tile, before that tile's first loads of W
             if constexpr (!XO) {
                 if (r + 1 == R)
-                    load_x(xn);
+                    load_x(xn, true);
             }
             float acc[NB];
 #pragma unroll
@@ -826,7 +830,8 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
     const uint32_t KV = row_bytes / 16u;
     const uint32_t n_chunks = (KV + kMfmaChunkSlices - 1u) / kMfmaChunkSlices;
     const uint64_t pmask = (1ull << shift) - 1ull;
-    const Rsrc x_rsrc = make_rsrc(x, nb * row_bytes);
+    // (of no bytes in a workgroup without tiles, such as one outside the mask)
+    auto x_rsrc = [&](bool live) __attribute__((always_inline)) { return make_rsrc(x, live ? nb * row_bytes : 0u); };
     uint32_t bad = 0u;
     const uint32_t w_sl = threadIdx.x % kMfmaChunkSlices;
     const uint32_t w_r = __builtin_amdgcn_readfirstlane(threadIdx.x / kMfmaChunkSlices);
@@ -866,38 +871,42 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         return (uint32_t)__builtin_amdgcn_readfirstlane(
             cl >= n_chunks ? n_chunks : (cl + rot >= n_chunks ? cl + rot - n_chunks : cl + rot));
     };
-    auto load_x = [&](uint32_t c, u32x4 *xv) __attribute__((always_inline)) {
+    auto load_x = [&](const Rsrc &r, uint32_t c, u32x4 *xv) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < (XA ? 0 : XL); ++q) {
             const uint32_t L = (uint32_t)q * kMfmaThreads + threadIdx.x;
             const uint32_t b = L / kMfmaChunkSlices, kv = c * kMfmaChunkSlices + L % kMfmaChunkSlices;
-            xv[q] = buf_load(x_rsrc, b < nb && kv < KV ? b * row_bytes + kv * 16u : kXOutside);
+            xv[q] = buf_load(r, b < nb && kv < KV ? b * row_bytes + kv * 16u : kXOutside);
         }
     };
-    auto load_rows = [&](const Tile &d, uint32_t c, int s) __attribute__((always_inline)) {
+    auto load_rows = [&](const Tile &d, const Rsrc &r, uint32_t c, int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < WL; ++q)
             ws[s][q] = buf_load_nt(row_rsrc(d.at[q], d.on[q], row_bytes), c * kMfmaChunk + w_sl * 16u);
-        load_x(c, xs[s]);
+        load_x(r, c, xs[s]);
     };
     Tile cur;
+    bool live = false;
     auto prime = [&](uint32_t t) __attribute__((always_inline)) {
         uint32_t raw[WL];
         load_entries(t, raw);
         cur = tile_of(t, raw);
+        live = t < n_tiles;
+        const Rsrc r = x_rsrc(live);
 #pragma unroll
         for (int s = 0; s < kMfmaSets; ++s)
-            load_rows(cur, chunk_at((uint32_t)s, cur.rot), s);
+            load_rows(cur, r, chunk_at((uint32_t)s, cur.rot), s);
     };
     auto prologue = [&]() __attribute__((always_inline)) {
         if (XA) {
             constexpr uint32_t kSl = kXaBytes / 16u;
+            const Rsrc r = x_rsrc(live);
 #pragma unroll
             for (int q = 0; q < XB * (int)kSl / kMfmaThreads; ++q) {
                 const uint32_t i = (uint32_t)q * kMfmaThreads + threadIdx.x;
                 const uint32_t b = i / kSl, sl = i % kSl;
                 *reinterpret_cast<u32x4 *>(&s_xa[b][sl * 16u]) =
-                    buf_load(x_rsrc, b < nb && sl < KV ? b * row_bytes + sl * 16u : kXOutside);
+                    buf_load(r, b < nb && sl < KV ? b * row_bytes + sl * 16u : kXOutside);
             }
         }
     };
@@ -905,6 +914,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
         const uint32_t m0 = t * (uint32_t)ROWS;
         const uint32_t m_end = min(m0 + (uint32_t)ROWS, M);
         const uint32_t rot = cur.rot;
+        const Rsrc xr = x_rsrc(true);
         uint32_t raw[WL];  // used a tile's chunks later, so that nothing waits for it
         load_entries(next, raw);
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -946,7 +956,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
 #pragma unroll
             for (int s = 0; s < kMfmaSets; ++s)
                 step(c + (uint32_t)s, s, [&]() __attribute__((always_inline)) {
-                    load_rows(cur, chunk_at(last ? (uint32_t)s : c + (uint32_t)(kMfmaSets + s), cur.rot), s);
+                    load_rows(cur, xr, chunk_at(last ? (uint32_t)s : c + (uint32_t)(kMfmaSets + s), cur.rot), s);
                 });
         }
         s_red[wave][lane] = acc;
