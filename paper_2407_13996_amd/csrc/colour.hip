@@ -694,7 +694,8 @@ static int launch_classify(Ctx *c, const HashArgs &h, const TableArgs &tab,
     const uint32_t tile = cls_wave_tile(slices ? kPhasedLoads : kClsLoads);
     const uint64_t n_tiles = ((n & ~15ull) + tile - 1) / tile;
     // (the bound of 1024-address tiles, whatever the tile)
-    if (n / cls_wave_tile(kClsLoads) >= (1ull << 31) - 1u)
+    const uint32_t small = cls_wave_tile(kClsLoads);
+    if (((n & ~15ull) + small - 1) / small >= (1ull << 31))
         return set_error(SGDRC_EINVAL, "n too large");
     // grid sizing counts workgroups' worth of tiles
     const uint64_t wg_tiles = (n_tiles + kClsWaves - 1) / kClsWaves;
