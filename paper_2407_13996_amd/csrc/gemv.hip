@@ -329,7 +329,7 @@ __device__ __forceinline__ uint64_t tile_phys(const uint8_t *w_pool, uint32_t en
 constexpr int kRingWgsPerCu = 5;
 constexpr uint64_t kRingRowsPerPage = 32;
 
-template <int WT, int XT, int NB, int R, int U, bool XO>
+template <int WT, int XT, int NB, int R, int U>
 __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
     const uint8_t *__restrict__ w_pool, const uint32_t *__restrict__ pt, uint64_t pool_pages,
     uint32_t M, uint32_t K, const uint8_t *__restrict__ x, uint32_t nb, float *__restrict__ y,
@@ -446,15 +446,9 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
     };
     auto body = [&](uint32_t t, uint32_t next, uint32_t, uint32_t &) __attribute__((always_inline)) {
         const uint32_t m0 = t * R;
-        uint32_t xn[XO ? 1 : U][XO ? 1 : NB][XO ? 1 : XW];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const Row nxt = row_of(r + 1 < R ? m0 + r + 1u : next < n_tiles ? next * R : M);
-            // x of the next tile, before that tile's first loads of W
-            if constexpr (!XO) {
-                if (r + 1 == R)
-                    load_x(xn, true);
-            }
             float acc[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -510,15 +504,6 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv_ring(
                 y[(uint64_t)b * M + m0 + r] = v;
         }
         ph ^= 1u;
-        if constexpr (!XO) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int i = 0; i < XW; ++i)
-                        xk[u][b][i] = xn[u][b][i];
-        }
     };
     static_tile_stream(g, n_tiles, prime, NoOp(), body, NoOp());
     if (bad)
@@ -1132,20 +1117,20 @@ static GemvKernel ring_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype
     if (p.path != SGDRC_GEMV_VALU || w_dtype != x_dtype || slots > p.loads ||
         (page_bytes % row_bytes && row_bytes * kRingRowsPerPage > page_bytes))
         return nullptr;
-#define SGDRC_RING(NB, R, U, XO)                                                       \
-    if (p.batch_cols == NB && p.rows == R && slots == U && p.x_once == (XO ? 1u : 0u)) { \
-        if (w_dtype == SGDRC_BF16)                                                     \
-            return k_gemv_ring<SGDRC_BF16, SGDRC_BF16, NB, R, U, XO>;                  \
-        return w_dtype == SGDRC_F16 ? k_gemv_ring<SGDRC_F16, SGDRC_F16, NB, R, U, XO>  \
-                                    : k_gemv_ring<SGDRC_F32, SGDRC_F32, NB, R, U, XO>; \
+#define SGDRC_RING(NB, R, U)                                                     \
+    if (p.batch_cols == NB && p.rows == R && slots == U) {                       \
+        if (w_dtype == SGDRC_BF16)                                               \
+            return k_gemv_ring<SGDRC_BF16, SGDRC_BF16, NB, R, U>;                \
+        return w_dtype == SGDRC_F16 ? k_gemv_ring<SGDRC_F16, SGDRC_F16, NB, R, U>  \
+                                    : k_gemv_ring<SGDRC_F32, SGDRC_F32, NB, R, U>; \
     }
-    SGDRC_RING(1, 2, 6, true)
-    SGDRC_RING(1, 2, 5, true)
-    SGDRC_RING(1, 2, 4, true)
-    SGDRC_RING(1, 2, 3, true)
-    SGDRC_RING(1, 4, 2, false)
-    SGDRC_RING(2, 4, 3, true)
-    SGDRC_RING(2, 4, 2, true)
+    SGDRC_RING(1, 2, 6)
+    SGDRC_RING(1, 2, 5)
+    SGDRC_RING(1, 2, 4)
+    SGDRC_RING(1, 2, 3)
+    SGDRC_RING(1, 4, 2)
+    SGDRC_RING(2, 4, 3)
+    SGDRC_RING(2, 4, 2)
 #undef SGDRC_RING
     return nullptr;
 }
