@@ -604,6 +604,25 @@ __device__ __forceinline__ void gated_tile_loop(const Gate &g, uint32_t n_tiles,
         raise_flag(g.err, err);
 }
 
+// After a static launch's tiles: ``tail`` in worker 0, the time log's partial end
+// stamp, the error bits.
+template <typename Tail>
+__device__ __forceinline__ void static_end(const Gate &g, uint32_t a, Tail tail, uint32_t err)
+{
+    if (a == 0u && blockIdx.x < g.n_xcd)
+        tail();
+    if (g.tlog) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_fetch_max(&g.q->tpart[(blockIdx.x % kTimePartials) * (kCounterStride / 2)],
+                                   (uint64_t)__builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (err != 0u)
+        raise_flag(g.err, err);
+}
+
 // Static schedule for launches whose CU mask is a union of whole XCDs (the
 // host sets g.statics).  The hardware hands the workgroups of a grid to the
 // XCDs by index modulo the XCD count (checked at context creation), so a
@@ -645,36 +664,35 @@ __device__ __forceinline__ void static_tile_stream(const Gate &g, uint32_t n_til
         log_tile(g, cu, t);
         body(t, t + workers, cu, err);
     }
-    if (a == 0u && blockIdx.x < g.n_xcd)
-        tail();
-    if (g.tlog) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (threadIdx.x == 0)
-            __hip_atomic_fetch_max(&g.q->tpart[(blockIdx.x % kTimePartials) * (kCounterStride / 2)],
-                                   (uint64_t)__builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (err != 0u)
-        raise_flag(g.err, err);
+    static_end(g, a, tail, err);
 }
 
-struct NoPrime {
-    __device__ void operator()(uint32_t) const {}
-};
-
 // The same for bodies that take one tile at a time (``prologue`` and ``body``
-// as in gated_tile_loop; ``claim`` has no effect).
+// as in gated_tile_loop; ``claim`` has no effect).  The first tile is worked
+// out only behind the prologue's loads: its divisions before them cost 0.2 us
+// of a 14 us launch (8192 x 1024 on 64 CUs).
 template <typename Prologue, typename Body, typename Tail = NoOp>
 __device__ __forceinline__ void static_tile_loop(const Gate &g, uint32_t n_tiles, Prologue prologue,
                                                  Body body, Tail tail = Tail())
 {
-    static_tile_stream(
-        g, n_tiles, NoPrime(), prologue,
-        [&](uint32_t t, uint32_t, uint32_t cu, uint32_t &err) __attribute__((always_inline)) {
+    uint32_t xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    const uint32_t a = g.xcd_rank[xcc & 0xFu];
+    const uint32_t cu = g.log_cu ? (my_cu_entry(g) & 0xFFFFu) : (uint32_t)kMaxCus;
+    prologue();
+    if (g.tlog && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(&g.tlog[0], __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    uint32_t err = 0u;
+    if (a != 0xFFu) {
+        const uint32_t workers = (gridDim.x / g.n_xcd) * g.n_allowed_xcd;
+        for (uint32_t t = (blockIdx.x / g.n_xcd) * g.n_allowed_xcd + a; t < n_tiles; t += workers) {
+            log_tile(g, cu, t);
             body(t, cu, err, NoOp());
-        },
-        tail);
+        }
+    }
+    static_end(g, a, tail, err);
 }
 
 // The gate's two schedules behind one call: static for masks of whole XCDs
