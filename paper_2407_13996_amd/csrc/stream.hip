@@ -57,8 +57,12 @@ constexpr int kStreamWgsPerCu = 1;
 // The shortest launches: tiles of 16 KiB, up to four workgroups per CU.
 constexpr int kSmallUnroll = 4;
 constexpr int kSmallWgsPerCu = 4;
-// Static schedule up to this many 64 KiB tiles per CU (see stream_plan).
-constexpr uint64_t kStaticTilesPerCu = 32;
+// Static schedule up to this many 64 KiB tiles per CU (see stream_plan): on up
+// to ``eighths`` of the CUs, on more, on all.
+struct StaticLimit {
+    uint64_t eighths, few, most, all;
+};
+constexpr StaticLimit kStaticTriad = {4, 32, 12, 28}, kStaticRelayout = {5, 32, 16, 32};
 // each workgroup of a preemptible launch hands back at most one tile
 static_assert(2 * kStreamWgsPerCu * kMaxCus <= (int)kHandBackCap, "hand-back ring too small");
 
@@ -372,13 +376,20 @@ __global__ __launch_bounds__(kStreamThreads) void k_triad(
 // How a launch over ``tiles64`` tiles of 64 KiB takes its tiles.  The queue
 // hands out one ticket per tile from one counter (about 12 ns each, so that
 // the 256 first tickets alone take 3 us) and counts arrivals at the end; the
-// static schedule has neither.  It is taken while a CU has at most
-// kStaticTilesPerCu tiles, beyond which the queue's even finish is worth as
-// much.  On MI355X, 64 KiB pages, 256 CUs, queue / static: triad of 3000001
-// elements 15.3 / 8.3 us, 33000000 73.8 / 66.0, 67000000 134.4 / 129.7,
-// 134000000 252.9 / 254.7; relayout of 32 MiB 21.4 / 13.4, 256 MiB 92.1 /
-// 86.9, 512 MiB 169.7 / 168.3, 1 GiB 331.5 / 332.8.  Preemptible launches
-// always take the queue, which their resumption continues.
+// static schedule has neither.  It is taken while a CU has at most ``limit``
+// tiles, beyond which the queue's even finish is worth as much.  Up to half of
+// the XCDs (five of eight for the relayout) are bound each by its own rate and
+// finish alike; more of them, but not all, share the HBM unevenly, so the queue
+// wins earlier.  On MI355X, 64 KiB
+// pages, queue / static in us by tiles per CU:
+//   triad     64 CUs: 10 59.7 / 56.7, 32 170 / 167;  160: 12 78.3 / 75.7, 16 101.0 /
+//             102.8, 32 190.5 / 196.5;  192: 12 87.9 / 88.4, 16 113.1 / 116.0, 32
+//             214.8 / 226.9;  224: 16 119.6 / 116.9, 32 225.5 / 230.9;  256: 2.5 29.2 /
+//             24.0, 16 136.6 / 131.4, 28 224.1 / 220.9, 32 255.2 / 256.5, 40 312 / 316
+//   relayout  64: 32 125.9 / 117.3;  160: 32 133.3 / 127.2;  192: 16 78.7 / 78.0, 24
+//             112.5 / 114.7, 32 146.0 / 151.2;  224: 24 118.4 / 117.2, 32 153.3 / 154.7;
+//             256: 2.5 24.3 / 17.0, 16 92.3 / 86.9, 32 170.1 / 169.5, 40 209 / 211
+// Preemptible launches always take the queue, which their resumption continues.
 //
 // With at most one 64 KiB tile per CU, tiles of 16 KiB put more CUs to work
 // (static schedule only): triad of 3000001 elements in 2 KiB pages 9.2 / 8.5
@@ -388,10 +399,11 @@ struct StreamPlan {
     bool statics, small;
 };
 
-static StreamPlan stream_plan(Ctx *c, void *stream, uint64_t tiles64, bool ev)
+static StreamPlan stream_plan(Ctx *c, void *stream, uint64_t tiles64, bool ev, const StaticLimit &l)
 {
-    const uint64_t cus = ev ? 0u : (uint64_t)static_cus(c, stream);
-    return {cus && tiles64 <= kStaticTilesPerCu * cus, cus && tiles64 <= cus};
+    const uint64_t cus = ev ? 0u : (uint64_t)static_cus(c, stream), all = (uint64_t)c->num_cus;
+    const uint64_t limit = cus == all ? l.all : 8u * cus > l.eighths * all ? l.most : l.few;
+    return {cus && tiles64 <= limit * cus, cus && tiles64 <= cus};
 }
 
 static uint64_t tiles_of(uint64_t n_bytes, uint32_t tile)
@@ -423,7 +435,7 @@ int bimodal_relayout(sgdrc_ctx *ctx, const sgdrc_paged *dst, const sgdrc_paged *
     if (tiles64 >= (1ull << 31))
         return set_error(SGDRC_EINVAL, "n_bytes too large");
     const bool ev = stream_preemptible(c, stream);
-    const StreamPlan plan = stream_plan(c, stream, tiles64, ev);
+    const StreamPlan plan = stream_plan(c, stream, tiles64, ev, kStaticRelayout);
     const uint64_t n_tiles = plan.small ? tiles_of(n_bytes, Geo<US>::kTile) : tiles64;
     if (ev && (rc = discard_suspended(c, stream)))
         return rc;
@@ -494,7 +506,7 @@ int bimodal_relayout_batch(sgdrc_ctx *ctx, const sgdrc_relayout_item *items, uin
                 return set_error(SGDRC_EINVAL, "items %u..%u: too many bytes for one launch", first,
                                  first + i);
         }
-        const StreamPlan plan = stream_plan(c, stream, tiles64, false);
+        const StreamPlan plan = stream_plan(c, stream, tiles64, false, kStaticRelayout);
         const uint32_t tile = plan.small ? Geo<US>::kTile : Geo<U>::kTile;
         RelayoutBatch b{};
         uint64_t tiles = 0;
@@ -550,7 +562,7 @@ int colored_stream(sgdrc_ctx *ctx, const sgdrc_paged *a, const sgdrc_paged *b,
     const uint64_t tiles64 = tiles_of(n_bytes, ev ? Geo<UE>::kTile : Geo<U>::kTile);
     if (tiles64 >= (1ull << 31))
         return set_error(SGDRC_EINVAL, "n_elems too large");
-    const StreamPlan plan = stream_plan(c, stream, tiles64, ev);
+    const StreamPlan plan = stream_plan(c, stream, tiles64, ev, kStaticTriad);
     const uint64_t n_tiles = plan.small ? tiles_of(n_bytes, Geo<US>::kTile) : tiles64;
     if (ev && (rc = discard_suspended(c, stream)))
         return rc;

@@ -133,3 +133,24 @@ def test_bad_page_in_small_and_static_launches(ctx):
             lo, hi = bad << shift, min((bad + 1) << shift, n_bytes)
             assert bool((dst[lo:hi] == 0xEE).all()) and bool((dst[n_bytes:] == 0xEE).all())
             assert torch.equal(dst[:lo], src[:lo]) and torch.equal(dst[hi:n_bytes], src[hi:n_bytes])
+
+
+# the static schedule's last size and the queue's first on five, six and all eight XCDs
+@pytest.mark.parametrize("triad,cus,per_cu", [(True, 160, 12), (True, 192, 12), (True, 256, 28), (False, 160, 32),
+                                              (False, 192, 16), (True, 128, 32), (False, 256, 32)])
+def test_schedule_line_by_mask(ctx, triad, cus, per_cu):
+    shift = 16
+    for tiles, schedule in ((per_cu * cus, "static"), (per_cu * cus + 1, "queue")):
+        say(f"{'triad' if triad else 'relayout'} of {tiles} tiles on {cus} CUs")
+        ident = torch.arange(tiles, dtype=torch.int32, device=DEV)
+        b, c = (torch.randint(-1000, 1000, (tiles << shift - 2,), device=DEV).float() for _ in range(2))
+        a = torch.full_like(b, -1.0)
+        pa, pb, pc = (sg.paged(t, ident, tiles) for t in (a, b, c))
+        sg.set_cu_mask(ctx, None, range(cus))
+        if triad:
+            sg.colored_stream(ctx, pa, pb, pc, 3.0, b.numel(), shift)
+        else:
+            sg.bimodal_relayout(ctx, pa, pb, 4 * b.numel(), shift)
+        assert (ctx.last_schedule(), ctx.last_tiles()) == (schedule, tiles)
+        sg.set_cu_mask(ctx, None, None)
+        assert torch.equal(a, b + 3 * c if triad else b)   # (whole numbers: exact either way)
