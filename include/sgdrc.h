@@ -445,8 +445,9 @@ int colored_gemv(sgdrc_ctx *ctx, const sgdrc_paged *w, int w_dtype, uint32_t M, 
  * meets on its way into y (the fp32 additions and FMAs of the kernel's fixed summation
  * tree, each MFMA counted as up to 32 additions), so that
  * |y - exact| <= sum_depth * 2^-24 * sum_k |W[m][k] x[b][k]| to first order
- * (products of bf16 or f16 operands are exact in fp32).  Lets tests and
- * tools see which kernel a configuration runs.  EINVAL: allowed_cus outside
+ * (products of bf16 or f16 operands are exact in fp32).  With
+ * colored_gemv_form, lets tests and tools see which kernel a configuration
+ * runs.  EINVAL: allowed_cus outside
  * 1..256, NULL out, or a shape colored_gemv rejects. */
 enum { SGDRC_GEMV_VALU = 0, SGDRC_GEMV_MFMA = 1 };
 typedef struct {
@@ -461,6 +462,20 @@ typedef struct {
 
 int colored_gemv_plan(uint32_t allowed_cus, int w_dtype, uint32_t M, uint32_t K, int x_dtype,
                     uint32_t batch, sgdrc_gemv_plan *out);
+
+/* The form of the plan's kernel that colored_gemv launches under a schedule
+ * (sgdrc_last_schedule) for pages of 2^page_shift bytes (host-only, no
+ * context, no device):
+ * SGDRC_GEMV_BY_TILES loads a tile, sums it and goes on to the next;
+ * SGDRC_GEMV_RING (vector path) and SGDRC_GEMV_STREAM (MFMA) load on into the
+ * workgroup's next tile, under SGDRC_SCHED_STATIC only.  *loads is the plan's
+ * loads, or for the ring the 16-byte loads per lane that a row needs.  The
+ * form changes no result.  EINVAL: as colored_gemv_plan, an unknown schedule,
+ * a page_shift colored_gemv rejects, NULL form or loads. */
+enum { SGDRC_GEMV_BY_TILES = 0, SGDRC_GEMV_RING = 1, SGDRC_GEMV_STREAM = 2 };
+int colored_gemv_form(uint32_t allowed_cus, uint32_t schedule, int w_dtype, uint32_t M, uint32_t K,
+                      int x_dtype, uint32_t batch, uint32_t page_shift, uint32_t *form,
+                      uint32_t *loads);
 
 /* ---------------------------------------------------- bimodal tensors
  *

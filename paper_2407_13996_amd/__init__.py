@@ -127,6 +127,7 @@ def lib() -> ctypes.CDLL:
                                i32),
             "colored_gemv": ([vp, P(Paged), i32, u32, u32, vp, i32, u32, vp, u32, vp], i32),
             "colored_gemv_plan": ([u32, i32, u32, u32, i32, u32, P(GemvPlan)], i32),
+            "colored_gemv_form": ([u32, u32, i32, u32, u32, i32, u32, u32, P(u32), P(u32)], i32),
             "colour_classify_table": ([vp, P(ColourTable), vp, u64, vp, vp, vp], i32),
             "colour_alloc_pagetable_table": ([vp, P(ColourTable), u64, u32, u64, P(ColourSet), u64,
                                               vp, P(u64), vp], i32),
@@ -442,6 +443,18 @@ def gemv_plan(allowed_cus: int, w_dtype: int, M: int, K: int, x_dtype: int, batc
     return {"path": "mfma" if p.path == GEMV_MFMA else "valu", "rows": p.rows, "loads": p.loads,
             "batch_cols": p.batch_cols, "tiles": p.tiles, "sum_depth": p.sum_depth,
             "x_once": bool(p.x_once)}
+
+
+def gemv_form(allowed_cus: int, schedule: str, w_dtype: int, M: int, K: int, x_dtype: int, batch: int,
+              page_shift: int) -> tuple:
+    """(form, loads): the form of the plan's kernel that colored_gemv launches
+    under ``schedule`` ("static" or "queue"), "tiles", "ring" or "stream", and its
+    loads per lane (host-only; no device needed)."""
+    form, loads = ctypes.c_uint32(), ctypes.c_uint32()
+    _check(lib().colored_gemv_form(int(allowed_cus), {"queue": 0, "static": 1}[schedule], int(w_dtype), int(M),
+                                   int(K), int(x_dtype), int(batch), int(page_shift), ctypes.byref(form),
+                                   ctypes.byref(loads)))
+    return ("tiles", "ring", "stream")[form.value], loads.value
 
 
 class Bimodal:

@@ -1106,19 +1106,40 @@ static GemvKernel valu_kernel(const sgdrc_gemv_plan &p)
     return nullptr;
 }
 
-// The ring kernel of a vector plan whose rows one round of loads covers, for
-// W and x of one type; launched under the static schedule only (the queues
-// name a tile too late to load ahead).  Its ring has as many loads as a row
-// needs (the plan's ``loads`` at most).
-static GemvKernel ring_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype, uint64_t row_bytes,
-                              uint64_t page_bytes)
+// Which form of a plan's kernel a launch takes, and its loads per lane.  Under
+// the static schedule (the queues name a tile too late to load ahead):
+//
+// The ring form of a vector plan whose rows one round of loads covers, for W
+// and x of one type.  Its ring has as many loads as a row needs, from two on.
+//
+// The streaming form of an MFMA plan, for rows that never cross pages (a page
+// holds a whole number of them; pages are powers of two, so a row is one too),
+// where workgroups (two per CU) take more than one tile: with x for the whole K
+// in LDS, more than two (11008 x 4096 batch 4 on 192 CUs, four calls: 87.4 us by
+// tiles, 88.7 streaming; on 128 CUs 122.8 and 119.2).  With one tile each there
+// is no tile end to run over (4096 x 8192 batch 8: 63.1 and 65.5 us).
+struct Form {
+    uint32_t form, loads;
+};
+
+static Form make_form(const sgdrc_gemv_plan &p, bool statics, uint32_t allowed, int w_dtype,
+                      int x_dtype, uint64_t row_bytes, uint64_t page_bytes)
 {
     const uint64_t slots = (row_bytes + kGemvThreads * 16u - 1u) / (kGemvThreads * 16u);
-    if (p.path != SGDRC_GEMV_VALU || w_dtype != x_dtype || slots > p.loads ||
-        (page_bytes % row_bytes && row_bytes * kRingRowsPerPage > page_bytes))
-        return nullptr;
+    const bool whole_rows = page_bytes % row_bytes == 0u;
+    if (statics && p.path == SGDRC_GEMV_VALU && w_dtype == x_dtype && p.batch_cols <= 2u &&
+        slots >= 2u && slots <= p.loads && (whole_rows || row_bytes * kRingRowsPerPage <= page_bytes))
+        return {SGDRC_GEMV_RING, (uint32_t)slots};
+    if (statics && p.path == SGDRC_GEMV_MFMA && whole_rows &&
+        p.tiles > (p.x_once ? 4u : 2u) * (uint64_t)allowed)
+        return {SGDRC_GEMV_STREAM, p.loads};
+    return {SGDRC_GEMV_BY_TILES, p.loads};
+}
+
+static GemvKernel ring_kernel(const sgdrc_gemv_plan &p, int w_dtype, uint32_t loads)
+{
 #define SGDRC_RING(NB, R, U)                                                     \
-    if (p.batch_cols == NB && p.rows == R && slots == U) {                       \
+    if (p.batch_cols == NB && p.rows == R && loads == U) {                       \
         if (w_dtype == SGDRC_BF16)                                               \
             return k_gemv_ring<SGDRC_BF16, SGDRC_BF16, NB, R, U>;                \
         return w_dtype == SGDRC_F16 ? k_gemv_ring<SGDRC_F16, SGDRC_F16, NB, R, U>  \
@@ -1169,12 +1190,6 @@ static GemvKernel plan_kernel(const sgdrc_gemv_plan &p, int w_dtype, int x_dtype
     }
 }
 
-// The streaming form of an MFMA plan's kernel, under the static schedule, for
-// rows that never cross pages (a page holds a whole number of them), where
-// workgroups (two per CU) take more than one tile: with x for the whole K in
-// LDS, more than two (11008 x 4096 batch 4 on 192 CUs, four calls: 87.4 us by
-// tiles, 88.7 streaming; on 128 CUs 122.8 and 119.2).  With one tile each there is no tile end to run over (4096 x 8192
-// batch 8: 63.1 and 65.5 us).
 template <int DT>
 static GemvKernel stream_kernel_dt(const sgdrc_gemv_plan &p)
 {
@@ -1183,15 +1198,6 @@ static GemvKernel stream_kernel_dt(const sgdrc_gemv_plan &p)
     if (p.batch_cols == 4)
         return p.rows == 16 ? k_gemm_stream<DT, 16, 4, false> : k_gemm_stream<DT, 8, 4, false>;
     return p.rows == 16 ? k_gemm_stream<DT, 16, 8, false> : k_gemm_stream<DT, 8, 8, false>;
-}
-
-static GemvKernel stream_kernel(const sgdrc_gemv_plan &p, int w_dtype, uint64_t row_bytes,
-                                uint64_t page_bytes, int allowed)
-{
-    if (p.path != SGDRC_GEMV_MFMA || page_bytes % row_bytes ||
-        p.tiles <= (p.x_once ? 4u : 2u) * (uint64_t)allowed)
-        return nullptr;
-    return w_dtype == SGDRC_BF16 ? stream_kernel_dt<SGDRC_BF16>(p) : stream_kernel_dt<SGDRC_F16>(p);
 }
 
 static int kernel_occupancy(GemvKernel k, int threads)
@@ -1246,6 +1252,28 @@ int colored_gemv_plan(uint32_t allowed_cus, int w_dtype, uint32_t M, uint32_t K,
     return SGDRC_OK;
 }
 
+int colored_gemv_form(uint32_t allowed_cus, uint32_t schedule, int w_dtype, uint32_t M, uint32_t K,
+                      int x_dtype, uint32_t batch, uint32_t page_shift, uint32_t *form,
+                      uint32_t *loads)
+{
+    clear_error();
+    if (!form || !loads)
+        return set_error(SGDRC_EINVAL, "form or loads is NULL");
+    if (schedule > SGDRC_SCHED_STATIC)
+        return set_error(SGDRC_EINVAL, "unknown schedule %u", schedule);
+    int rc = check_shift(page_shift);
+    if (rc)
+        return rc;
+    sgdrc_gemv_plan p;
+    if ((rc = colored_gemv_plan(allowed_cus, w_dtype, M, K, x_dtype, batch, &p)))
+        return rc;
+    const Form f = make_form(p, schedule == SGDRC_SCHED_STATIC, allowed_cus, w_dtype, x_dtype,
+                             (uint64_t)K * dtype_size(w_dtype), 1ull << page_shift);
+    *form = f.form;
+    *loads = f.loads;
+    return SGDRC_OK;
+}
+
 int colored_gemv(sgdrc_ctx *ctx, const sgdrc_paged *w, int w_dtype, uint32_t M, uint32_t K,
                  const void *d_x, int x_dtype, uint32_t batch, float *d_y, uint32_t page_shift,
                  void *stream)
@@ -1285,12 +1313,15 @@ int colored_gemv(sgdrc_ctx *ctx, const sgdrc_paged *w, int w_dtype, uint32_t M, 
     rc = make_gate(c, stream, plan.tiles, kGemvGroupCus, &g, &li, false, true);
     if (rc)
         return rc;
-    const uint64_t row_bytes = (uint64_t)K * dtype_size(w_dtype);
-    GemvKernel k = g.statics ? ring_kernel(plan, w_dtype, x_dtype, row_bytes, 1ull << page_shift) : nullptr;
-    const bool ring = k != nullptr;
-    if (!ring && g.statics)
-        k = stream_kernel(plan, w_dtype, row_bytes, 1ull << page_shift, li.allowed);
-    if (!k)
+    const Form f = make_form(plan, g.statics != 0u, (uint32_t)li.allowed, w_dtype, x_dtype,
+                             (uint64_t)K * dtype_size(w_dtype), 1ull << page_shift);
+    const bool ring = f.form == SGDRC_GEMV_RING;
+    GemvKernel k;
+    if (ring)
+        k = ring_kernel(plan, w_dtype, f.loads);
+    else if (f.form == SGDRC_GEMV_STREAM)
+        k = w_dtype == SGDRC_BF16 ? stream_kernel_dt<SGDRC_BF16>(plan) : stream_kernel_dt<SGDRC_F16>(plan);
+    else
         k = plan_kernel(plan, w_dtype, x_dtype);
     if (!k)
         return set_error(SGDRC_EINVAL, "no kernel for the plan (library fault)");

@@ -56,6 +56,27 @@ X_STAGED = [(1100, 4000, 4, BF16, BF16, 21, None), (700, 4096, 3, F16, F16, 12, 
 # tile's bytes): f16 beside the bf16 LS layers, and a K tail inside the round
 X_ONCE = [(200, 8192, 1, F16, F16, 16, 64), (300, 4096, 2, F16, F16, 16, None),
           (203, 11000, 1, BF16, BF16, 16, 64), (517, 4000, 2, BF16, BF16, 12, 100)]
+# the next rows' loads in flight over tile ends, under the static schedule: the
+# ring (batch 1-2, rows above 4 KiB; the shorter rows beside them take the tile
+# loop) and the streaming MFMA kernel (rows that divide the page); each also
+# on the masks below, the last of them partial: (M, K, batch, dtype, page shift)
+RING = [(1, 2048, 1, BF16, 21), (5, 8, 1, BF16, 16), (1031, 2056, 1, F16, 18), (2500, 4096, 1, BF16, 21),
+        (333, 4104, 1, BF16, 19), (701, 6144, 1, F16, 20), (411, 8184, 1, BF16, 21),
+        (300, 5120, 1, F32, 20), (513, 11008, 1, BF16, 21), (97, 12288, 1, F16, 21),
+        (2049, 4096, 2, BF16, 21), (700, 6136, 2, F16, 19), (1025, 1024, 2, F32, 17), (259, 3072, 2, F32, 20),
+        # fewer rows than a tile, one row
+        (1, 4096, 1, BF16, 21), (3, 11008, 1, BF16, 21), (1, 11008, 1, F16, 21), (2, 2048, 1, F32, 18),
+        (1, 6144, 2, F16, 21), (3, 4096, 2, BF16, 13),
+        # a page holds one, two or eight whole rows
+        (2500, 4096, 1, BF16, 13), (1100, 8192, 1, F16, 14), (701, 2048, 1, F32, 14), (2100, 4096, 2, BF16, 13),
+        (1031, 4096, 2, F16, 16)]
+RING_MASKS = [None, range(32), range(64, 128), range(100)]
+STREAM = [(1301, 4096, 8, BF16, 17), (2900, 4096, 4, BF16, 21), (1111, 2048, 6, F16, 16),
+          (1040, 8192, 5, F16, 18), (2100, 256, 3, BF16, 12), (1200, 16384, 4, BF16, 19),
+          (4000, 1024, 8, BF16, 16), (1050, 8, 8, F16, 10),
+          # one row a page: more entries than a tile stages
+          (1100, 4096, 8, BF16, 13), (1050, 8192, 4, F16, 14)]
+STREAM_MASKS = [range(32), range(96, 160), None, range(20)]
 CORUN_LS = [(4096, 11008, 1, BF16, BF16, 21, 192)]
 
 
@@ -69,7 +90,23 @@ def gpu_cases():
         cases += [(M, K, B, dt, dt, 16, n), (M, K, B, dt, dt, 16, -(-M // 16))]
     cases += [(M, K, B, BF16, BF16, 21, cus) for M, K in LS_LAYERS for B in LS_BATCHES
               for cus in LS_CUS]
+    for shapes, masks in ((RING, RING_MASKS), (STREAM, STREAM_MASKS)):
+        cases += [(M, K, B, dt, dt, shift, None if cus is None else len(cus))
+                  for M, K, B, dt, shift in shapes for cus in masks]
     return cases
+
+
+def schedule(cus):
+    """The schedule of a launch on the first ``cus`` CUs (None: all): static for
+    whole XCDs of 32."""
+    return "static" if (NUM_CUS if cus is None else cus) % 32 == 0 else "queue"
+
+
+def bench_spread_cases():
+    """Those of them that it also times with the CUs spread over all XCDs (the
+    ticket queues)."""
+    return [(M, K, B, BF16, BF16, 21, cus) for M, K in LS_LAYERS for B in (1, 8) for cus in LS_CUS
+            if cus < NUM_CUS]
 
 
 def bench_cases():

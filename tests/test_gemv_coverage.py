@@ -1,7 +1,7 @@
 """CPU check: every GEMV kernel variant a benchmark configuration launches
 is launched by some GPU parity test as well.  The variant comes from the
-library's host-only plan query (colored_gemv_plan), the same function
-colored_gemv launches by."""
+library's host-only queries (colored_gemv_plan, colored_gemv_form), the same
+functions colored_gemv launches by."""
 import pytest
 
 import gemv_cases as gc
@@ -9,22 +9,64 @@ import gemv_cases as gc
 sg = pytest.importorskip("paper_2407_13996_amd")
 
 
-def _variant(case):
+def _variant(case, schedule):
     M, K, B, wd, xd, shift, cus = case
-    p = sg.gemv_plan(gc.NUM_CUS if cus is None else cus, wd, M, K, xd, B)
+    n = gc.NUM_CUS if cus is None else cus
+    p = sg.gemv_plan(n, wd, M, K, xd, B)
+    form, loads = sg.gemv_form(n, schedule, wd, M, K, xd, B, shift)
     esize = 4 if wd == gc.F32 else 2
-    whole = -(-(M * K * esize) // (1 << shift)) <= 256   # table staged once per workgroup
-    return (p["path"], p["rows"], p["loads"], p["batch_cols"], p["x_once"], wd, xd, whole)
+    # (the tile loops) table staged once per workgroup
+    whole = form != "tiles" or -(-(M * K * esize) // (1 << shift)) <= 256
+    return (schedule, p["path"], form, p["rows"], loads, p["batch_cols"], p["x_once"], wd, xd, whole)
 
 
 def test_every_benchmarked_gemv_variant_is_gpu_tested():
-    tested = {_variant(c) for c in gc.gpu_cases()}
+    tested = {_variant(c, gc.schedule(c[-1])) for c in gc.gpu_cases()}
+    timed = [(c, gc.schedule(c[-1])) for c in gc.bench_cases()] + [(c, "queue") for c in gc.bench_spread_cases()]
     missing = {}
-    for c in gc.bench_cases():
-        v = _variant(c)
+    for c, schedule in timed:
+        v = _variant(c, schedule)
         if v not in tested:
             missing[v] = c
     assert not missing, f"benchmarked GEMV variants no GPU test reaches: {missing}"
+
+
+def test_form_rules():
+    """Which form of a plan's kernel a launch takes: the ring for batch 1-2, rows
+    of two loads per lane or more in one round, one type, pages of 32 rows or of
+    whole rows; the streaming MFMA kernel for rows that divide the page and more
+    than two tiles per CU (four with x in LDS); both under the static schedule
+    only."""
+    def form(cus, M, K, B, shift=21, wd=gc.BF16, xd=None, schedule="static"):
+        return sg.gemv_form(cus, schedule, wd, M, K, wd if xd is None else xd, B, shift)
+    for cus in (64, 128, 192, 256):
+        assert form(cus, 4096, 11008, 1) == ("ring", 6)
+        assert form(cus, 11008, 4096, 1) == ("ring", 2) == form(cus, 11008, 4096, 2)
+        assert form(cus, 4096, 11008, 2) == ("tiles", 3)                   # two rounds
+        assert form(cus, 4096, 2048, 1) == ("tiles", 2)                    # one load per lane
+        assert form(cus, 4096, 2056, 1) == ("ring", 2)
+        assert form(cus, 4096, 11008, 1, xd=gc.F32)[0] == "tiles"
+        assert form(cus, 4096, 11008, 1, schedule="queue") == ("tiles", 6)
+        assert form(cus, 11008, 4096, 8)[0] == "stream"
+        assert form(cus, 11008, 4096, 8, schedule="queue")[0] == "tiles"
+        assert form(cus, 4096, 11008, 8)[0] == "tiles"                     # rows cross pages
+    assert form(256, 3000, 6000, 1, shift=16)[0] == "tiles"                # 64 KiB: under 32 rows
+    assert form(256, 3000, 8192, 1, shift=14) == ("ring", 4)               # one whole row a page
+    assert [form(c, 11008, 4096, 4)[0] for c in (64, 128, 192)] == ["stream", "stream", "tiles"]
+    assert form(64, 16 * 128, 4096, 8)[0] == "tiles" and form(64, 16 * 128 + 1, 4096, 8)[0] == "stream"
+
+
+def test_form_rejects_bad_arguments():
+    L = sg.lib()
+    import ctypes
+    f, n = ctypes.c_uint32(), ctypes.c_uint32()
+    ok = (64, 1, gc.BF16, 16, 16, gc.BF16, 1, 16)
+    assert L.colored_gemv_form(*ok, ctypes.byref(f), ctypes.byref(n)) == sg.OK
+    assert L.colored_gemv_form(*ok, None, ctypes.byref(n)) == sg.EINVAL
+    assert L.colored_gemv_form(*ok, ctypes.byref(f), None) == sg.EINVAL
+    for i, bad in ((0, 0), (0, 257), (1, 2), (2, 3), (4, 12), (6, 9), (7, 9), (7, 40)):
+        args = ok[:i] + (bad,) + ok[i + 1:]
+        assert L.colored_gemv_form(*args, ctypes.byref(f), ctypes.byref(n)) == sg.EINVAL, args
 
 
 def test_plan_matches_the_c3_sweep_expectations():

@@ -9,6 +9,7 @@ import sys
 import numpy as np
 import pytest
 
+import gemv_cases as gc
 import paper_2407_13996_amd as sg
 import test_gpu_parity as tp
 
@@ -25,24 +26,22 @@ def ctx():
     c.close()
 
 
-# (M, K, batch, dtype, page shift); K * 2 divides the page
-CASES = [(1301, 4096, 8, sg.BF16, 17), (2900, 4096, 4, sg.BF16, 21), (1111, 2048, 6, sg.F16, 16),
-         (1040, 8192, 5, sg.F16, 18), (2100, 256, 3, sg.BF16, 12), (1200, 16384, 4, sg.BF16, 19),
-         (4000, 1024, 8, sg.BF16, 16), (1050, 8, 8, sg.F16, 10),
-         # one row a page: more entries than a tile stages
-         (1100, 4096, 8, sg.BF16, 13), (1050, 8192, 4, sg.F16, 14)]
-
-
-@pytest.mark.parametrize("M,K,B,dt,shift", CASES)
+@pytest.mark.parametrize("M,K,B,dt,shift", gc.STREAM)
 def test_stream_equals_oracle_and_queue(ctx, orc, M, K, B, dt, shift):
     print(f"gemm stream {M}x{K} B={B} dtype {dt} pages 2^{shift}", file=sys.stderr, flush=True)
     pool, pt, d_pool, d_pt, pool_pages = tp.upload_w(orc, M, K, dt, shift, range(48), M + K, 1, 6)
     xb = tp.x_bits(dt, B * K, M)
     ref, absdot = orc.gemv(pool, pt, dt, M, K, xb, dt, B, shift)
     ys = []
-    for cus in (list(range(32)), list(range(96, 160)), None, list(range(20))):
-        y = tp.launch_gemv(ctx, d_pool, d_pt, pool_pages, M, K, B, dt, dt, tp.to_dev(xb), shift, tp.cu_list(cus))
-        tp.gemv_check(ctx, y, ref, absdot, M, K, B, dt, dt, tp.cu_list(cus), tag="stream")
+    for cus in gc.STREAM_MASKS:
+        n = ctx.num_cus if cus is None else len(cus)
+        y = tp.launch_gemv(ctx, d_pool, d_pt, pool_pages, M, K, B, dt, dt, tp.to_dev(xb), shift, cus)
+        schedule = ctx.last_schedule()
+        assert schedule == gc.schedule(n)
+        form, _ = sg.gemv_form(n, schedule, dt, M, K, dt, B, shift)
+        if cus is gc.STREAM_MASKS[0]:
+            assert form == "stream"
+        tp.gemv_check(ctx, y, ref, absdot, M, K, B, dt, dt, cus, tag="stream")
         ys.append(y.view(np.uint32))
     assert all((y == ys[0]).all() for y in ys[1:])
 

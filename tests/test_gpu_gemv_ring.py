@@ -1,14 +1,16 @@
 """Batch 1-2 GEMV under the static schedule (the ring kernel: the next rows'
 loads stay in flight) against the oracle and, bit for bit, against the queue
 schedule (a partial mask; the tile loop): every ring length, rows that cross a
-page end, row and slice remainders, more and fewer tiles than workgroups, small
-pages of one or a few whole rows, tables of more than 2048 entries, and
-page-table entries outside the pool."""
+page end, row and slice remainders, more and fewer tiles than workgroups, fewer
+rows than a tile, small pages of one or a few whole rows, tables of more than
+2048 entries, and page-table entries outside the pool.  Rows of 4 KiB or less
+take the tile loop on every mask."""
 import sys
 
 import numpy as np
 import pytest
 
+import gemv_cases as gc
 import paper_2407_13996_amd as sg
 import synth
 import test_gpu_parity as tp
@@ -27,26 +29,23 @@ def ctx():
     c.close()
 
 
-# (M, K, batch, dtype, page shift): rows of 1 to 24 KiB
-CASES = [(1, 2048, 1, BF16, 21), (5, 8, 1, BF16, 16), (1031, 2056, 1, F16, 18), (2500, 4096, 1, BF16, 21),
-         (333, 4104, 1, BF16, 19), (701, 6144, 1, F16, 20), (411, 8184, 1, BF16, 21),
-         (300, 5120, 1, F32, 20), (513, 11008, 1, BF16, 21), (97, 12288, 1, F16, 21),
-         (2049, 4096, 2, BF16, 21), (700, 6136, 2, F16, 19), (1025, 1024, 2, F32, 17), (259, 3072, 2, F32, 20),
-         # a page holds one, two or eight whole rows
-         (2500, 4096, 1, BF16, 13), (1100, 8192, 1, F16, 14), (701, 2048, 1, F32, 14), (2100, 4096, 2, BF16, 13),
-         (1031, 4096, 2, F16, 16)]
-
-
-@pytest.mark.parametrize("M,K,B,dt,shift", CASES)
+@pytest.mark.parametrize("M,K,B,dt,shift", gc.RING)
 def test_ring_equals_oracle_and_queue(ctx, orc, M, K, B, dt, shift):
     print(f"gemv ring {M}x{K} B={B} dtype {dt} pages 2^{shift}", file=sys.stderr, flush=True)
     pool, pt, d_pool, d_pt, pool_pages = tp.upload_w(orc, M, K, dt, shift, range(48), M + K, 1, 6)
     xb = tp.x_bits(dt, B * K, M)
     ref, absdot = orc.gemv(pool, pt, dt, M, K, xb, dt, B, shift)
     ys = []
-    for cus in (None, list(range(32)), list(range(64, 128)), list(range(100))):
-        y = tp.launch_gemv(ctx, d_pool, d_pt, pool_pages, M, K, B, dt, dt, tp.to_dev(xb), shift, tp.cu_list(cus))
-        tp.gemv_check(ctx, y, ref, absdot, M, K, B, dt, dt, tp.cu_list(cus), tag="ring")
+    for cus in gc.RING_MASKS:
+        n = ctx.num_cus if cus is None else len(cus)
+        y = tp.launch_gemv(ctx, d_pool, d_pt, pool_pages, M, K, B, dt, dt, tp.to_dev(xb), shift, cus)
+        schedule = ctx.last_schedule()
+        assert schedule == gc.schedule(n)
+        form, loads = sg.gemv_form(n, schedule, dt, M, K, dt, B, shift)
+        row = K * (4 if dt == F32 else 2)
+        want = ("ring", -(-row // 4096)) if schedule == "static" and row > 4096 else ("tiles", loads)
+        assert (form, loads) == want
+        tp.gemv_check(ctx, y, ref, absdot, M, K, B, dt, dt, cus, tag="ring")
         ys.append(y.view(np.uint32))
     assert all((y == ys[0]).all() for y in ys[1:])
 
