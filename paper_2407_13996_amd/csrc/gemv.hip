@@ -789,11 +789,11 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4)
 // entries are scalar loads, made when a tile begins and used in its last chunks.
 //
 // HBM-bound with the x staging beside it: bf16, 11008 x 4096 in 2 MiB pages, four
-// calls with 12 rotated copies on MI355X, by tiles / streaming: batch 8 on 256
-// CUs 76.9 / 72.4 us (73.0 with the entries resolved where they are loaded; 71.5
-// with the whole table staged in LDS, which 64 KiB pages do not allow: 89.6
-// against 85.8 us there); with the staged table, 192 CUs 96.1 / 89.1, 128 139.5 /
-// 126.7, 64 212.3 / 184.5; batch 4 on 128 CUs 122.8 / 119.2, 64 175.4 / 164.6.
+// calls with 16 rotated copies on MI355X, by tiles / streaming: batch 8 on 256
+// CUs 77.3 / 73.6 us, 192 96.9 / 90.1, 128 139.8 / 127.9, 64 212.6 / 182.6; batch
+// 4 on 128 CUs 123.6 / 117.1, 64 176.1 / 159.7.  (Entries resolved where they are
+// loaded cost 0.8 percent on 256 CUs; the whole table staged in LDS saved 1, but
+// 64 KiB pages do not allow it: 89.6 by tiles against 85.8 us there.)
 template <int DT, int ROWS, int XB, bool XA>
 __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm_stream(
     const uint8_t *__restrict__ w_pool, const uint32_t *__restrict__ pt, uint64_t pool_pages,
@@ -1004,8 +1004,12 @@ static int dtype_size(int dt) { return dt == SGDRC_F32 ? 4 : 2; }
 // 16-row tiles fill unevenly), since a row costs more in an 8-row tile (x is
 // read twice as often per W byte); the same bits either way.  Over M =
 // 1536..8192 rows of 4096 and 11008, batch 4 and 8, on 64..256 CUs this is
-// never more than 5 percent slower than the better height (a rule of one to
-// two 16-row tiles per CU was up to 26 percent slower).
+// never more than 5 percent slower than the better height by tiles (a rule of
+// one to two 16-row tiles per CU was up to 26 percent slower).  It holds for
+// the streaming form where that is launched (make_form): 2048..14336 rows of 1024
+// to 8192, 8 / 16 rows, 6144 x 4096 batch 8 on 256 CUs (8 by the rule) 49.2 / 54.0
+// us, 11008 x 4096 (16) 83.2 / 73.6, on 64 CUs 238.8 / 182.6; the worst, 11008 x
+// 4096 batch 4 on 128 CUs, 111.9 / 117.1 (16).
 static sgdrc_gemv_plan make_plan(uint32_t allowed, int w_dtype, uint32_t M, uint32_t K,
                                  int x_dtype, uint32_t batch)
 {
@@ -1115,9 +1119,15 @@ static GemvKernel valu_kernel(const sgdrc_gemv_plan &p)
 // The streaming form of an MFMA plan, for rows that never cross pages (a page
 // holds a whole number of them; pages are powers of two, so a row is one too),
 // where workgroups (two per CU) take more than one tile: with x for the whole K
-// in LDS, more than two (11008 x 4096 batch 4 on 192 CUs, four calls: 87.4 us by
-// tiles, 88.7 streaming; on 128 CUs 122.8 and 119.2).  With one tile each there
-// is no tile end to run over (4096 x 8192 batch 8: 63.1 and 65.5 us).
+// in LDS, more than two.  Beyond these lines no shape was slower by streaming
+// (rows of 2 to 16 KiB, 64..256 CUs); at or below them it won and lost by shape.
+// bf16, four calls in us, by tiles / streaming: batch 4 above four tiles per CU
+// 8192 x 4096 on 64 CUs 138.9 / 124.5, 14336 x 2048 on 192 67.4 / 65.4; between two
+// and four 11008 x 4096 on 192 CUs 88.3 / 86.8, 6144 x 4096 on 128 71.4 / 72.4, at
+// two 8192 x 2048 on 256 39.4 / 42.6, 8192 x 1024 29.2 / 31.6.  Batch 8 above two
+// tiles per CU 8192 x 8192 on 192 CUs 129.3 / 125.2, at two 8192 x 2048 on 256 40.9 /
+// 41.6, at one, with no tile end to run over, 4096 x 8192 64.0 / 60.1, 4096 x 2048
+// 29.1 / 28.0.
 struct Form {
     uint32_t form, loads;
 };
