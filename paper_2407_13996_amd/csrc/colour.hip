@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "host_common.hpp"
 
@@ -109,13 +110,23 @@ constexpr int kClsTableWgsPerCu = 6;
 // the wavefronts of an XCD start together and keep step (one that runs ahead
 // waits for the misses that those behind it then hit), so a slice's lines
 // are fetched about once per XCD while all of them use it.  2^24 addresses on
-// MI355X, plain / by slices: 8 MiB table 165 / 104 us, 16 MiB 235 / 123, 64
-// MiB 308 / 214; with 1024 addresses per wavefront 182 us for 16 MiB, with
-// 1 MiB slices 127 us; a 4 MiB table 91 / 94 us.
+// MI355X, plain / by slices: 8 MiB table 164 / 99 us, 16 MiB 232 / 119, 64
+// MiB 307 / 200; with 1024 addresses per wavefront 182 us for 16 MiB, with
+// 1 MiB slices 127 us; a 4 MiB table 91 / 94 us.  Two workgroups per CU: three,
+// which fit without a histogram, keep step less well (16 MiB 125 us, 32 MiB 166
+// against 154).
+//
+// That is for addresses in any order.  Where neighbouring ones lie in one line of
+// the table (ascending addresses, runs of a page's lines), there is little to
+// miss and a pass over the slices only costs time, so a wavefront looks at two
+// of its lanes' indices and then gathers all of them plainly; otherwise it
+// passes over the slices outside the range of its indices.  2^24 addresses in
+// steps of one partition, plain kernel / every slice / now: 8 MiB table 34.6 /
+// 39.9 / 29.0 us, 16 MiB 39.8 / 51.1 / 30.1, 64 MiB 39.5 / 114 / 29.9.
 constexpr int kPhasedLoads = 32;
 constexpr uint32_t kPhasedGroup = 16;  // gathers in flight per lane
 constexpr uint32_t kSliceShift = 21;
-constexpr int kPhasedWgsPerCu = 4;
+constexpr int kPhasedWgsPerCu = 2;
 
 // Histogram bins are replicated 16 times in LDS (copy = lane mod 16,
 // bin-major), so that lanes of a wavefront seldom add to one address.  More
@@ -148,13 +159,26 @@ __device__ __forceinline__ void publish_histogram(uint64_t *hist_acc, uint64_t *
 // out: colours.  A lane whose index lies in another slice takes an offset past
 // the buffer resource, for which the hardware makes no access.  A finished
 // index is replaced by its colour with the upper bits set, which no slice
-// matches (the host keeps tables below 2^31 entries here).
+// matches (the host keeps tables below 2^31 entries here).  Slices outside the
+// range of the wavefront's indices are passed over.
 template <int N>
 __device__ __forceinline__ void gather_slices(const TableArgs &t, uint32_t (&c)[N])
 {
     const Rsrc r = make_rsrc(t.lut, (uint32_t)t.entries);
     const uint32_t slices = ((uint32_t)t.entries + (1u << kSliceShift) - 1u) >> kSliceShift;
+    // (as a signed number 0xFFFFFFFF is below every index)
+    uint32_t first = c[0];
+    int32_t last = (int32_t)c[0];
+#pragma unroll
+    for (int j = 1; j < N; ++j) {
+        first = min(first, c[j]);
+        last = max(last, (int32_t)c[j]);
+    }
+    const uint32_t q0 = first >> kSliceShift;
+    const int32_t q1 = last >> kSliceShift;
     for (uint32_t q = 0; q < slices; ++q) {
+        if (!__any(q >= q0 && (int32_t)q <= q1))
+            continue;
 #pragma unroll
         for (int g = 0; g < N; g += (int)kPhasedGroup) {
             uint32_t v[kPhasedGroup];
@@ -170,6 +194,32 @@ __device__ __forceinline__ void gather_slices(const TableArgs &t, uint32_t (&c)[
 #pragma unroll
     for (int j = 0; j < N; ++j)
         c[j] &= 0xFFu;
+}
+
+// The same in one pass.
+template <int N>
+__device__ __forceinline__ void gather_plain(const TableArgs &t, uint32_t (&c)[N])
+{
+    const Rsrc r = make_rsrc(t.lut, (uint32_t)t.entries);
+#pragma unroll
+    for (int g = 0; g < N; g += (int)kPhasedGroup) {
+        uint32_t v[kPhasedGroup];
+#pragma unroll
+        for (int j = 0; j < (int)kPhasedGroup; ++j)
+            v[j] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, c[g + j], 0, 0);
+#pragma unroll
+        for (int j = 0; j < (int)kPhasedGroup; ++j)
+            c[g + j] = c[g + j] == 0xFFFFFFFFu ? 255u : v[j];
+    }
+}
+
+// Whether neighbouring lanes' indices mostly lie in one 128-byte line, by two of
+// the lane's indices: a plain gather then fetches few lines, however large the
+// table.
+__device__ __forceinline__ bool gathers_share_lines(uint32_t c0, uint32_t c1)
+{
+    const uint32_t p0 = __shfl_xor(c0, 1, 64), p1 = __shfl_xor(c1, 1, 64);
+    return __popcll(__ballot(c0 >> 7 == p0 >> 7)) + __popcll(__ballot(c1 >> 7 == p1 >> 7)) >= 64;
 }
 
 // Where colours come from: the XOR hash, or a colour table in device memory
@@ -211,49 +261,75 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
         for (int j = 0; j < LOADS; ++j)
             v[j] = buf_load_nt(ra, (j * 64u + lane) * 16u);
         claim();
-        uint32_t tc[TAB ? 2 * LOADS : 1];
-        if (TAB) {
+        auto addr = [&](int j) __attribute__((always_inline)) {
+            const u32x4 &w = v[j / 2];
+            return j & 1 ? ((uint64_t)w.w << 32) | w.z : ((uint64_t)w.y << 32) | w.x;
+        };
+        const Rsrc rc = make_rsrc(colours + base, valid);
+        // the 1024 addresses of loads 8 q .. 8 q + 7, address j of a lane with
+        // colour(j), to LDS and the histogram
+        auto put = [&](int q, auto &&colour) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < 2 * LOADS; ++j) {
-                const u32x4 &w = v[j / 2];
-                const uint64_t a = j & 1 ? ((uint64_t)w.w << 32) | w.z : ((uint64_t)w.y << 32) | w.x;
-                if (FROM == ClsFrom::Table) {
-                    tc[TAB ? j : 0] = table_colour(tab, a);
-                } else {
-                    const uint64_t i = (a - tab.origin) >> tab.shift;
-                    tc[TAB ? j : 0] = a >= tab.origin && i < tab.entries ? (uint32_t)i : 0xFFFFFFFFu;
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t c0 = colour(2 * j), c1 = colour(2 * j + 1);
+                const uint32_t at = (uint32_t)(8 * q + j) * 64u + lane;
+                s_col[wave][at] = (uint16_t)(c0 | (c1 << 8));
+                // both addresses of the load are valid or neither (valid is even);
+                // invalid ones (read as address 0, a bin in range) add 0, so
+                // that no branch splits the lanes around the atomics (with one,
+                // the histogram cost several microseconds more)
+                if (HIST) {
+                    const uint32_t inc = 2u * at < valid ? 1u : 0u;
+                    atomicAdd(&s_hist[c0 * kCopies + copy], inc);
+                    atomicAdd(&s_hist[c1 * kCopies + copy], inc);
                 }
             }
-            if constexpr (FROM == ClsFrom::Slices)
-                gather_slices<2 * LOADS>(tab, tc);
-        }
+        };
+        // and the colours of N such groups to memory
+        auto store = [&](auto count) __attribute__((always_inline)) {
+            constexpr int N = decltype(count)::value;
+            // LDS accesses of one wavefront complete in order; the wave
+            // barriers only keep the compiler from moving these accesses
+            __builtin_amdgcn_wave_barrier();
+            u32x4 out[N];
 #pragma unroll
-        for (int j = 0; j < LOADS; ++j) {
-            const uint32_t c0 = TAB ? tc[TAB ? 2 * j : 0] : colour_lut(s_lut, v[j].x, v[j].y);
-            const uint32_t c1 = TAB ? tc[TAB ? 2 * j + 1 : 0] : colour_lut(s_lut, v[j].z, v[j].w);
-            s_col[wave][j * 64u + lane] = (uint16_t)(c0 | (c1 << 8));
-            // both addresses of the load are valid or neither (valid is even);
-            // invalid ones (read as address 0, a bin in range) add 0, so
-            // that no branch splits the lanes around the atomics (with one,
-            // the histogram cost several microseconds more)
-            if (HIST) {
-                const uint32_t inc = 2u * (j * 64u + lane) < valid ? 1u : 0u;
-                atomicAdd(&s_hist[c0 * kCopies + copy], inc);
-                atomicAdd(&s_hist[c1 * kCopies + copy], inc);
+            for (int i = 0; i < N; ++i)
+                out[i] = *reinterpret_cast<const u32x4 *>(&s_col[wave][i * 512u + lane * 8u]);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                buf_store_sc1(rc, i * 1024u + lane * 16u, out[i]);
+        };
+        using One = std::integral_constant<int, 1>;
+        if constexpr (FROM == ClsFrom::Hash) {
+            put(0, [&](int j) __attribute__((always_inline)) {
+                const u32x4 &w = v[j / 2];
+                return j & 1 ? colour_lut(s_lut, w.z, w.w) : colour_lut(s_lut, w.x, w.y);
+            });
+            store(One());
+        } else if constexpr (FROM == ClsFrom::Table) {
+            uint32_t c[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                c[j] = table_colour(tab, addr(j));
+            put(0, [&](int j) __attribute__((always_inline)) { return c[j]; });
+            store(One());
+        } else {
+            uint32_t c[2 * LOADS];
+#pragma unroll
+            for (int j = 0; j < 2 * LOADS; ++j) {
+                const uint64_t a = addr(j), i = (a - tab.origin) >> tab.shift;
+                c[j] = a >= tab.origin && i < tab.entries ? (uint32_t)i : 0xFFFFFFFFu;
             }
+            if (gathers_share_lines(c[0], c[9]))
+                gather_plain<2 * LOADS>(tab, c);
+            else
+                gather_slices<2 * LOADS>(tab, c);
+#pragma unroll
+            for (int q = 0; q < LOADS / 8; ++q)
+                put(q, [&](int j) __attribute__((always_inline)) { return c[16 * q + j]; });
+            store(std::integral_constant<int, LOADS / 8>());
         }
-        // LDS accesses of one wavefront complete in order; the wave
-        // barriers only keep the compiler from moving these accesses
-        __builtin_amdgcn_wave_barrier();
-        u32x4 out[LOADS / 8];
-#pragma unroll
-        for (int q = 0; q < LOADS / 8; ++q)
-            out[q] = *reinterpret_cast<const u32x4 *>(&s_col[wave][q * 512u + lane * 8u]);
-        __builtin_amdgcn_wave_barrier();
-        const Rsrc rc = make_rsrc(colours + base, valid);
-#pragma unroll
-        for (int q = 0; q < LOADS / 8; ++q)
-            buf_store_sc1(rc, q * 1024u + lane * 16u, out[q]);
     };
     auto flush = [&]() {
         if (HIST) {
@@ -324,7 +400,7 @@ __global__ __launch_bounds__(kClsThreads) void k_classify(const uint64_t *__rest
 }
 
 template <bool HIST>
-__global__ __launch_bounds__(kClsThreads) void k_classify_slices(const uint64_t *__restrict__ addrs,
+__global__ __launch_bounds__(kClsThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_classify_slices(const uint64_t *__restrict__ addrs,
                                                                  uint64_t n,
                                                                  uint8_t *__restrict__ colours,
                                                                  HashArgs h, TableArgs tab,
@@ -670,15 +746,16 @@ static HashArgs hash_args(const sgdrc_hash *h)
     return a;
 }
 
-// Whether a table is gathered slice by slice: larger than an XCD's L2, few
+// Whether a table is gathered slice by slice: larger than an XCD's L2 by half
+// (5 MiB, plain / by slices: 3 x 2^21 addresses 42.3 / 44.8 us; 6 MiB 48.3 / 46.7), few
 // enough slices (each costs the wavefronts an instruction per index; measured
 // up to 32), and enough addresses that a line fetched by an XCD is used
 // several times (n / 8 addresses per XCD against entries / 128 lines) and all
 // wavefronts have a tile.  Plain / by slices on MI355X: 2^22 addresses, 8 MiB
-// 45 / 32 us, 16 MiB 62 / 37; 2^21 addresses, 8 MiB 25 / 31 us.
+// 43 / 28 us, 16 MiB 60 / 35; 2^21 addresses, 8 MiB 25 / 31 us.
 static bool gather_by_slices(const TableArgs &t, uint64_t n)
 {
-    return t.entries > (2ull << kSliceShift) && t.entries <= (32ull << kSliceShift) &&
+    return t.entries >= (3ull << kSliceShift) && t.entries <= (32ull << kSliceShift) &&
            n >= t.entries / 4u && n >= (1ull << 22);
 }
 
