@@ -119,8 +119,7 @@ constexpr int kClsTableWgsPerCu = 6;
 // That is for addresses in any order.  Where neighbouring ones lie in one line of
 // the table (ascending addresses, runs of a page's lines), there is little to
 // miss and a pass over the slices only costs time, so a wavefront looks at two
-// of its lanes' indices and then gathers all of them plainly; otherwise it
-// passes over the slices outside the range of its indices.  2^24 addresses in
+// of its lanes' indices and then gathers all of them plainly.  2^24 addresses in
 // steps of one partition, plain kernel / every slice / now: 8 MiB table 34.6 /
 // 39.9 / 29.0 us, 16 MiB 39.8 / 51.1 / 30.1, 64 MiB 39.5 / 114 / 29.9.
 constexpr int kPhasedLoads = 32;
@@ -159,13 +158,12 @@ __device__ __forceinline__ void publish_histogram(uint64_t *hist_acc, uint64_t *
 // out: colours.  A lane whose index lies in another slice takes an offset past
 // the buffer resource, for which the hardware makes no access.  A finished
 // index is replaced by its colour with the upper bits set, which no slice
-// matches (the host keeps tables below 2^31 entries here).  Slices outside the
-// range of the wavefront's indices are passed over.
+// matches (the host keeps tables below 2^31 entries here).  Only the slices from
+// the wavefront's lowest index to its highest are gathered.
 template <int N>
 __device__ __forceinline__ void gather_slices(const TableArgs &t, uint32_t (&c)[N])
 {
     const Rsrc r = make_rsrc(t.lut, (uint32_t)t.entries);
-    const uint32_t slices = ((uint32_t)t.entries + (1u << kSliceShift) - 1u) >> kSliceShift;
     // (as a signed number 0xFFFFFFFF is below every index)
     uint32_t first = c[0];
     int32_t last = (int32_t)c[0];
@@ -174,11 +172,14 @@ __device__ __forceinline__ void gather_slices(const TableArgs &t, uint32_t (&c)[
         first = min(first, c[j]);
         last = max(last, (int32_t)c[j]);
     }
-    const uint32_t q0 = first >> kSliceShift;
-    const int32_t q1 = last >> kSliceShift;
-    for (uint32_t q = 0; q < slices; ++q) {
-        if (!__any(q >= q0 && (int32_t)q <= q1))
-            continue;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        first = min(first, (uint32_t)__shfl_xor((int)first, off, 64));
+        last = max(last, __shfl_xor(last, off, 64));
+    }
+    const uint32_t q0 = (uint32_t)__builtin_amdgcn_readfirstlane(first) >> kSliceShift;
+    const int32_t q1 = __builtin_amdgcn_readfirstlane(last) >> kSliceShift;
+    for (uint32_t q = q0; (int32_t)q <= q1; ++q) {  // (no index: 2047 and -1)
 #pragma unroll
         for (int g = 0; g < N; g += (int)kPhasedGroup) {
             uint32_t v[kPhasedGroup];
@@ -265,13 +266,13 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
             const u32x4 &w = v[j / 2];
             return j & 1 ? ((uint64_t)w.w << 32) | w.z : ((uint64_t)w.y << 32) | w.x;
         };
-        const Rsrc rc = make_rsrc(colours + base, valid);
         // the 1024 addresses of loads 8 q .. 8 q + 7, address j of a lane with
         // colour(j), to LDS and the histogram
         auto put = [&](int q, auto &&colour) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const uint32_t c0 = colour(2 * j), c1 = colour(2 * j + 1);
+                const uint32_t c0 = colour(2 * j);
+                const uint32_t c1 = colour(2 * j + 1);
                 const uint32_t at = (uint32_t)(8 * q + j) * 64u + lane;
                 s_col[wave][at] = (uint16_t)(c0 | (c1 << 8));
                 // both addresses of the load are valid or neither (valid is even);
@@ -296,6 +297,7 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
             for (int i = 0; i < N; ++i)
                 out[i] = *reinterpret_cast<const u32x4 *>(&s_col[wave][i * 512u + lane * 8u]);
             __builtin_amdgcn_wave_barrier();
+            const Rsrc rc = make_rsrc(colours + base, valid);
 #pragma unroll
             for (int i = 0; i < N; ++i)
                 buf_store_sc1(rc, i * 1024u + lane * 16u, out[i]);
@@ -303,8 +305,7 @@ __device__ __forceinline__ void classify(const uint64_t *__restrict__ addrs, uin
         using One = std::integral_constant<int, 1>;
         if constexpr (FROM == ClsFrom::Hash) {
             put(0, [&](int j) __attribute__((always_inline)) {
-                const u32x4 &w = v[j / 2];
-                return j & 1 ? colour_lut(s_lut, w.z, w.w) : colour_lut(s_lut, w.x, w.y);
+                return j & 1 ? colour_lut(s_lut, v[j / 2].z, v[j / 2].w) : colour_lut(s_lut, v[j / 2].x, v[j / 2].y);
             });
             store(One());
         } else if constexpr (FROM == ClsFrom::Table) {
@@ -399,8 +400,12 @@ __global__ __launch_bounds__(kClsThreads) void k_classify(const uint64_t *__rest
                                                                        hist_acc, hist_out, n_tiles, g);
 }
 
+// (without a histogram the compiler is told of the two wavefronts per SIMD: it
+// then keeps all of a slice's gathers in flight, 2^24 addresses in order through a
+// 16 MiB table 30.1 against 33.4 us; with one the default is better, at random
+// 119.9 against 122.6 us)
 template <bool HIST>
-__global__ __launch_bounds__(kClsThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_classify_slices(const uint64_t *__restrict__ addrs,
+__global__ __launch_bounds__(kClsThreads, HIST ? 0 : 2) void k_classify_slices(const uint64_t *__restrict__ addrs,
                                                                  uint64_t n,
                                                                  uint8_t *__restrict__ colours,
                                                                  HashArgs h, TableArgs tab,
