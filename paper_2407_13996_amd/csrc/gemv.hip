@@ -1045,14 +1045,18 @@ static sgdrc_gemv_plan make_plan(uint32_t allowed, int w_dtype, uint32_t M, uint
         p.rows = 4u;
         p.loads = long_rows && batch <= 2 ? 3u : 2u;
         // wide batches hold x of every batch row per slice in flight: with
-        // one slice (8 columns; 4 when an element of x is wider than one of W)
-        // twice the wavefronts fit, which wins as soon as a CU has more than
-        // one tile.  MI355X, four calls, two slices / one: bf16 W with fp32 x,
-        // 11008 x 4096 batch 5 on 256 CUs 260.9 / 148.1 us, batch 3 112.0 /
-        // 93.6, 4096 x 8192 batch 8 on 64 CUs 587.1 / 365.9; fp32, 4096 x 4096
-        // batch 8 93.3 / 88.7, 1000 x 2000 (one tile per CU) 31.2 / 33.3.
+        // one slice twice the wavefronts fit, which wins as soon as a CU has
+        // more than two tiles (8 columns; 4 when an element of x is wider than
+        // one of W), with fp32 x beside 16-bit W at 8 columns more than one.
+        // MI355X, K = 512..13824 on 64 and 256 CUs, one slice against two:
+        // fp32, 8 columns, up to two tiles per CU -1..+9 percent of the time,
+        // above -20..0; 16-bit W with fp32 x -33..-13 and -42..-22, at 4
+        // columns -7..+7 and -24..-2; the other mixes -6..+10 and -22..+4.
+        // bf16 W with fp32 x, four calls, 11008 x 4096 batch 5 on 256 CUs 260.9 /
+        // 148.1 us, batch 3 112.0 / 93.6.
         const bool x_wider = dtype_size(x_dtype) > dtype_size(w_dtype);
-        if ((M + 3u) / 4u > a && (p.batch_cols == 8u || (p.batch_cols == 4u && x_wider)))
+        const uint64_t t4 = (M + 3u) / 4u;
+        if (p.batch_cols == 8u ? t4 > (x_wider ? a : 2u * a) : p.batch_cols == 4u && x_wider && t4 > 2u * a)
             p.loads = 1u;
         const bool one_round6 = w_dtype == x_dtype && kv <= 6u * (uint64_t)kGemvThreads;
         if (batch <= 1 && long_rows && (few || one_round6)) {

@@ -56,6 +56,19 @@ def test_form_rules():
     assert form(64, 16 * 128, 4096, 8)[0] == "tiles" and form(64, 16 * 128 + 1, 4096, 8)[0] == "stream"
 
 
+def test_wide_batch_slices():
+    """Slices in flight of the vector path at batch 3-8: one above two four-row
+    tiles per CU (8 columns, or 4 with x wider than W), above one for fp32 x beside
+    16-bit W at 8 columns."""
+    def loads(tiles, wd, xd, B):
+        return sg.gemv_plan(64, wd, 4 * tiles - 3, 4096, xd, B)["loads"]
+    for wd, xd, B, line in ((gc.F32, gc.F32, 8, 128), (gc.F32, gc.BF16, 5, 128), (gc.BF16, gc.F16, 6, 128),
+                            (gc.BF16, gc.F32, 8, 64), (gc.F16, gc.F32, 5, 64), (gc.BF16, gc.F32, 4, 128),
+                            (gc.F16, gc.F32, 3, 128)):
+        assert (loads(line, wd, xd, B), loads(line + 1, wd, xd, B)) == (2, 1), (wd, xd, B)
+    assert loads(1000, gc.F32, gc.F32, 4) == 2 == loads(1000, gc.BF16, gc.F16, 3)
+
+
 def test_form_rejects_bad_arguments():
     L = sg.lib()
     import ctypes
